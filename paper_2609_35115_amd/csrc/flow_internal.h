@@ -24,6 +24,20 @@ namespace dcf {
 // Calls of at most this many rows (2 per stream and frame) run the skinny GEMM.
 constexpr int kSkinnyRows = 512;
 
+// Weights are packed in MFMA fragment order: [column block of 16][K step]
+// [lane][16 bytes], a K step being 32 (bf16) or 16 (fp32) values.  Lane l of
+// step s holds columns' K values: column l % 16 of the block, K values
+// s * 32 + 8 (l / 16) .. + 7 (bf16) or s * 16 + 4 (l / 16) .. + 3 (fp32).  One
+// fragment is one contiguous 1 KB load of a wave.  Columns past N are zeros;
+// K steps are padded with zeros to a multiple of kStepPad, so a loop over them
+// unrolls without a remainder.
+constexpr int kStepPad = 8;
+inline int k_steps(int K, bool bf16)
+{
+    const int kq = bf16 ? 32 : 16;
+    return (K + kStepPad * kq - 1) / (kStepPad * kq) * kStepPad;
+}
+
 enum Epi : int {
     E_H = 0,     // h = acc + bias                        (fp32)
     E_QKV = 1,   // q -> q buffer, k, v -> the carry      (operand type)
@@ -38,21 +52,24 @@ struct CarryRef {
     int Fr;                  // frames per region
     int Pr, Sl, R;           // prompt frames, slot frames, history slots
     const int64_t* hist;     // [B] chunks retained since the turn start
+    const int* slot;         // [B] hist mod (R + 1): the slot that the next call writes
     const int* plen;         // [B] prompt frames of the turn
 };
 
 // out[row][col] = epilogue(sum_k A[row][k] W[col][k] + bias[col]); with
 // ln_h set, A[row][k] = LN(ln_h[row])[k] * (1 + ln_scale[k]) + ln_shift[k]
-// (the modulated LayerNorm of the fp32 residual stream, K <= 512): normalised
-// while staged for calls of few rows, else written to A by a launch of its own.
+// (the modulated LayerNorm of the fp32 residual stream, K <= 512), normalised
+// while it is staged.
 struct GemmParams {
-    const void* A;           // [M][K] operand type (with ln_h: where the normalised operand may be written)
+    const void* A;           // [M][K] operand type (null with ln_h)
     const float* ln_h;       // [M][K] or null
     const float* ln_shift;   // [K]
     const float* ln_scale;   // [K]
-    const void* W;           // [N][K] operand type
+    const void* W;           // packed, operand type
     const float* bias;       // [N]
     int M, N, K;
+    int KS;                  // K steps of the packed weights (k_steps)
+    int groups, nsplit;      // many rows: column groups per wave, blocks per row tile
     float* h;                // E_H, E_RES: [M][N]
     const float* gate;       // E_RES: [N]
     void* out;               // E_GELU (operand type), E_VEL (fp32): [M][N]
@@ -117,8 +134,8 @@ hipError_t launch_euler(const EulerParams& p, int bf16, hipStream_t st);
 // Per-stream state: mode 0 begins a turn of stream b (no history, position
 // 0, no prompt), mode 1 ends its prompt pass (position and prompt = P),
 // mode 2 advances every stream by one retained chunk.
-hipError_t launch_advance(int64_t* hist, int64_t* pos, int* plen, int mode, int b, int P, int B, int f_chunk,
-                          hipStream_t st);
+hipError_t launch_advance(int64_t* hist, int64_t* pos, int* plen, int* slot, int mode, int b, int P, int B,
+                          int f_chunk, int R, hipStream_t st);
 // The carry of (stream b, branch, kv) at the step and block of c.base in
 // Eq. carry's logical order, widened to fp32: out [frames][heads * 64].
 hipError_t launch_carry_gather(const CarryRef& c, int b, int branch, int kv, int heads, int bf16, int frames,

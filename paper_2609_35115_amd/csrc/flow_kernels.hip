@@ -47,16 +47,30 @@ template <bool BF16> __device__ __forceinline__ void store1(void* base, size_t i
     else ((float*)base)[idx] = v;
 }
 
-__device__ __forceinline__ float gelu_tanh(float v)
+// GELU in its tanh form, 0.5 v (1 + tanh(y)) with y = sqrt(2/pi) (v + 0.044715 v^3),
+// as v / (1 + e^-2y): one exponential and one division instead of tanhf (whose
+// branches took about half of the MLP-up GEMM at 14,336 rows), and no
+// cancellation for negative v.
+template <bool BF16> __device__ __forceinline__ float gelu_tanh(float v)
 {
-    const float k0 = 0.7978845608028654f;   // sqrt(2 / pi)
-    return 0.5f * v * (1.0f + tanhf(k0 * (v + 0.044715f * v * v * v)));
+    const float k2 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;   // -2 sqrt(2 / pi) log2(e)
+    const float d = 1.0f + __builtin_amdgcn_exp2f(v * (k2 + k2 * 0.044715f * (v * v)));
+    if constexpr (BF16) return v * __builtin_amdgcn_rcpf(d);   // 1 ulp, rounded to bf16 next
+    else return v / d;
 }
 
-__device__ __forceinline__ float wave_sum(float v)
+// Sum over the 16 lanes of a DPP row, in every lane (rotations within the row:
+// one fixed order, no LDS round trip).
+template <int CTRL> __device__ __forceinline__ float row_ror(float v)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += row_ror<0x128>(v);   // row_ror:8, 4, 2, 1
+    v += row_ror<0x124>(v);
+    v += row_ror<0x122>(v);
+    v += row_ror<0x121>(v);
     return v;
 }
 
@@ -64,7 +78,7 @@ __device__ __forceinline__ float wave_sum(float v)
 __device__ __forceinline__ int own_base(const CarryRef& c, int prompt, int b)
 {
     if (prompt) return 0;
-    return c.Pr + (int)(c.hist[b] % (int64_t)(c.R + 1)) * c.Sl;
+    return c.Pr + c.slot[b] * c.Sl;
 }
 
 // ------------------------------------------------------------------- GEMM
@@ -109,7 +123,7 @@ __device__ __forceinline__ void epilogue4(const GemmParams& p, int row, int col,
     } else if constexpr (EPI == E_GELU) {
         f32x4 z;
 #pragma unroll
-        for (int r = 0; r < 4; r++) z[r] = gelu_tanh(y[r]);
+        for (int r = 0; r < 4; r++) z[r] = gelu_tanh<BF16>(y[r]);
         store4<BF16>(p.out, (size_t)row * p.N + col, z);
     } else if constexpr (EPI == E_VEL) {
         *(f32x4*)((float*)p.out + (size_t)row * p.N + col) = y;
@@ -173,138 +187,372 @@ __device__ __forceinline__ LnRow ln_row_stats(const float* h, int M, int K, int 
     return LnRow{x0 + md, 1.0f / sqrtf(var + 1e-6f)};
 }
 
-// Tiled GEMM for many rows: 4 waves as 2 x 2, each 16 MB rows x 16 NB
-// columns of MFMA blocks, so a block computes 32 MB x 32 NB.  K runs in
-// chunks of KC through two LDS buffers: the next chunk is loaded into
-// registers while the current one is multiplied, then stored into the other
-// buffer; one barrier per chunk.
-template <bool BF16, int EPI, int MB, int NB>
-__global__ __launch_bounds__(256) void gemm_kernel(const GemmParams p)
+// GEMM of many rows (calls of more than kSkinnyRows).  A block computes 16 MB
+// rows, each of its column waves all these rows of its own 16 NB columns (and,
+// of a LayerNorm operand, of p.groups such column groups one after another).
+// The activations sit in LDS, where every wave reads them; a weight fragment
+// is used by one wave only, so it goes from L2 straight to registers, in
+// fragment order, D steps ahead.
+//   LayerNorm operand: the block's rows are normalised into LDS once, all K
+//     (the launch of its own that this took wrote and read the operand again);
+//   plain operand: K runs in chunks through two LDS buffers, the next chunk
+//     loaded into registers while this one is multiplied.
+// Every output element adds its K steps in ascending order (with K partitions:
+// each partition's, then the partial sums in wave order), and a row's
+// LayerNorm sums have one order, so a row's result does not depend on the tile
+// or the batch.
+// What bounds it: at 14,336 rows the weight stream from L2 (64 rows per
+// fragment, about 64 B/clk per CU at the full matrix rate) and the epilogue's
+// vector work; at 1,792 rows load latency and the rows' LayerNorm, which every
+// column block repeats.  Us per launch, bf16, against 32 MB x 32 NB tiles with
+// both operands in LDS and a LayerNorm launch: 14,336 rows QKV 79.6 -> 44.3,
+// MLP up 95.3 -> 51.7, MLP down 55.4 -> 45.8; 1,792 rows 22.8 -> 16.8,
+// 22.7 -> 16.7, 20.7 -> 16.5.
+//
+// Waves of a block, and how many of them share its columns by splitting every
+// chunk of K between them.  8 waves halve how often rows are normalised and
+// weights read; 64 x 256-column tiles keep 4, since two such blocks per CU
+// run in different phases (QKV and MLP up at 14,336 rows: 44.3 and 51.7 us
+// with 4 waves, 63.0 and 59.9 with 8).  K >= 1024 runs 32 x 64 columns per
+// wave row with K in two partitions: twice the loads in flight per column
+// (MLP down at 1,792 rows: 16.5 us, against 17.7 without partitions and 20.7
+// with 16 x 64 tiles).
+template <int MB, int NB> constexpr int gemm_waves() { return MB == 4 && NB == 4 ? 4 : 8; }
+template <int MB, int NB> constexpr int gemm_ksplit() { return MB == 2 && NB == 2 ? 2 : 1; }
+
+// K values of an LDS row: the whole (padded) K of a LayerNorm operand, else a
+// chunk of kStepPad steps per K partition.
+template <bool BF16, bool LN, int KW> __host__ __device__ constexpr int panel_row(int KS)
 {
+    return (LN ? KS : KW * kStepPad) * (BF16 ? 32 : 16) + (BF16 ? 8 : 4);   // padded: conflict-free 16-byte reads
+}
+
+template <int EPI> constexpr bool ln_operand() { return EPI == E_QKV || EPI == E_GELU || EPI == E_VEL; }
+
+constexpr int kSkinnyBigK = 1024;   // K from which a GEMM of a plain operand splits K further
+
+// Where a row of the call goes (E_QKV): its q row, its carry region, its frame there.
+struct RowOut {
+    int64_t q, kv;
+    int frame, pad;
+};
+
+template <bool BF16, int EPI, int MB, int NB>
+__global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(const GemmParams p)
+{
+    constexpr int NW = gemm_waves<MB, NB>(), NT = 64 * NW;
+    constexpr int KW = ln_operand<EPI>() ? 1 : gemm_ksplit<MB, NB>(), NC = NW / KW;   // K partitions, column waves
+    constexpr int kChunk = KW * kStepPad;              // K steps of a plain operand's LDS buffer
     using T = typename std::conditional<BF16, uint16_t, float>::type;
-    constexpr int BM = 32 * MB, BN = 32 * NB;
-    constexpr int KC = (MB * NB <= 4 ? 128 : 64) / (BF16 ? 1 : 2);
-    constexpr int LD = KC + (BF16 ? 8 : 4);          // padded LDS row: conflict-free 16-byte reads
-    constexpr int VE = 16 / (int)sizeof(T);          // elements per 16-byte vector
-    constexpr int VPR = KC / VE;                     // vectors per tile row
-    constexpr int NVA = BM * VPR / 256, NVB = BN * VPR / 256;   // vectors per thread per operand
-    constexpr int KQ = BF16 ? 32 : 16;               // K of one MFMA step group
+    using Frag = typename std::conditional<BF16, bf16x8_t, f32x4>::type;
+    constexpr bool LN = ln_operand<EPI>();
+    constexpr int BM = 16 * MB;
+    constexpr int KQ = BF16 ? 32 : 16, VE = BF16 ? 8 : 4;
+    constexpr int D = NB >= 4 ? 4 : 8;                 // weight steps in flight
     extern __shared__ __align__(16) unsigned char smem[];
-    T* As = (T*)smem;                                // [2][BM * LD]
-    T* Bs = As + 2 * BM * LD;                        // [2][BN * LD]
+    const int LD = panel_row<BF16, LN, KW>(p.KS);
+    T* As = (T*)smem;                                  // [LN ? 1 : 2][BM][LD]
+    float* ss = (float*)(As + (size_t)BM * LD);        // LN: scale, shift
+    RowOut* ro = (RowOut*)(ss + 2 * p.K);              // E_QKV
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const T* A = (const T*)p.A;
-    const T* W = (const T*)p.W;
+    const int l16 = lane & 15, g = lane >> 4;
+    const int cs = blockIdx.x % p.nsplit, m0 = (blockIdx.x / p.nsplit) * BM;
+    const int N16 = (p.N + 15) >> 4;
+    const int kw = wave / NC;                          // K partition: kStepPad steps of every chunk
+    const int cb0 = (cs * p.groups * NC + wave % NC) * NB;   // the wave's first column block; groups are NC NB apart
 
-    u32x4 ra[NVA], rb[NVB];
-    const int kfull = p.K / KC;
-    auto gload = [&](int kc) {
-        if (kc < kfull) {
+    const u32x4* Wl = (const u32x4*)p.W + lane;
+    const u32x4* wn[NB];                               // fragments of the next steps to load
+    auto aim = [&](int grp) {
 #pragma unroll
-            for (int v = 0; v < NVA; v++) {
-                const int idx = tid + 256 * v, r = idx / VPR, kv = (idx % VPR) * VE;
-                ra[v] = *(const u32x4*)(A + (size_t)min(m0 + r, p.M - 1) * p.K + kc * KC + kv);
-            }
+        for (int j = 0; j < NB; j++) wn[j] = Wl + ((size_t)min(cb0 + grp * NC * NB + j, N16 - 1) * p.KS + kw * kStepPad) * 64;
+    };
+    u32x4 w[D][NB];
+    auto load_w = [&](int i) {
 #pragma unroll
-            for (int v = 0; v < NVB; v++) {
-                const int idx = tid + 256 * v, r = idx / VPR, kv = (idx % VPR) * VE;
-                rb[v] = *(const u32x4*)(W + (size_t)min(n0 + r, p.N - 1) * p.K + kc * KC + kv);
-            }
-        } else {   // a last partial chunk reads zeros past K
+        for (int j = 0; j < NB; j++) w[i][j] = wn[j][i * 64];
+    };
+    aim(0);
 #pragma unroll
-            for (int v = 0; v < NVA; v++) {
-                const int idx = tid + 256 * v, r = idx / VPR, kv = (idx % VPR) * VE, k = kc * KC + kv;
-                ra[v] = k < p.K ? *(const u32x4*)(A + (size_t)min(m0 + r, p.M - 1) * p.K + k) : u32x4{0, 0, 0, 0};
-            }
+    for (int i = 0; i < D; i++) load_w(i);
+
+    constexpr int NVA = (BM * kChunk * KQ / VE + NT - 1) / NT;   // a plain chunk's vectors per thread
+    constexpr int VPR = kChunk * KQ / VE;
+    u32x4 ra[NVA];
+    auto gload = [&](int c) {
 #pragma unroll
-            for (int v = 0; v < NVB; v++) {
-                const int idx = tid + 256 * v, r = idx / VPR, kv = (idx % VPR) * VE, k = kc * KC + kv;
-                rb[v] = k < p.K ? *(const u32x4*)(W + (size_t)min(n0 + r, p.N - 1) * p.K + k) : u32x4{0, 0, 0, 0};
-            }
+        for (int v = 0; v < NVA; v++) {
+            const int idx = tid + NT * v, r = min(idx / VPR, BM - 1), k = c * kChunk * KQ + (idx % VPR) * VE;
+            const u32x4 x = *(const u32x4*)((const T*)p.A + (size_t)min(m0 + r, p.M - 1) * p.K + min(k, p.K - VE));
+#pragma unroll
+            for (int e = 0; e < 4; e++) ra[v][e] = k < p.K ? x[e] : 0u;
         }
     };
     auto lstore = [&](int buf) {
 #pragma unroll
         for (int v = 0; v < NVA; v++) {
-            const int idx = tid + 256 * v, r = idx / VPR, kv = (idx % VPR) * VE;
-            *(u32x4*)(As + (size_t)buf * BM * LD + r * LD + kv) = ra[v];
-        }
-#pragma unroll
-        for (int v = 0; v < NVB; v++) {
-            const int idx = tid + 256 * v, r = idx / VPR, kv = (idx % VPR) * VE;
-            *(u32x4*)(Bs + (size_t)buf * BN * LD + r * LD + kv) = rb[v];
+            const int idx = tid + NT * v, r = idx / VPR, kv = (idx % VPR) * VE;
+            if (BM * VPR % NT == 0 || r < BM) *(u32x4*)(As + (size_t)(buf * BM + r) * LD + kv) = ra[v];
         }
     };
 
-    f32x4 acc[NB][MB];
-#pragma unroll
-    for (int i = 0; i < NB; i++)
-#pragma unroll
-        for (int j = 0; j < MB; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int l16 = lane & 15, g = lane >> 4;
-    const int nk = (p.K + KC - 1) / KC;
-    gload(0);
-    lstore(0);
-    __syncthreads();
-    for (int kc = 0; kc < nk; kc++) {
-        const int buf = kc & 1;
-        if (kc + 1 < nk) gload(kc + 1);
-        const T* Ab = As + (size_t)buf * BM * LD;
-        const T* Bb = Bs + (size_t)buf * BN * LD;
-#pragma unroll
-        for (int s = 0; s < KC / KQ; s++) {
-            if constexpr (BF16) {
-                bf16x8_t wf[NB], xf[MB];
-#pragma unroll
-                for (int i = 0; i < NB; i++) wf[i] = *(const bf16x8_t*)(Bb + (wn * 16 * NB + 16 * i + l16) * LD + KQ * s + 8 * g);
-#pragma unroll
-                for (int j = 0; j < MB; j++) xf[j] = *(const bf16x8_t*)(Ab + (wm * 16 * MB + 16 * j + l16) * LD + KQ * s + 8 * g);
-#pragma unroll
-                for (int i = 0; i < NB; i++)
-#pragma unroll
-                    for (int j = 0; j < MB; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i], xf[j], acc[i][j], 0, 0, 0);
-            } else {
-                f32x4 wf[NB], xf[MB];
-#pragma unroll
-                for (int i = 0; i < NB; i++) wf[i] = *(const f32x4*)(Bb + (wn * 16 * NB + 16 * i + l16) * LD + KQ * s + 4 * g);
-#pragma unroll
-                for (int j = 0; j < MB; j++) xf[j] = *(const f32x4*)(Ab + (wm * 16 * MB + 16 * j + l16) * LD + KQ * s + 4 * g);
-#pragma unroll
-                for (int q = 0; q < 4; q++)
-#pragma unroll
-                    for (int i = 0; i < NB; i++)
-#pragma unroll
-                        for (int j = 0; j < MB; j++)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[i][q], xf[j][q], acc[i][j], 0, 0, 0);
+    if constexpr (LN) {
+        for (int k4 = tid; k4 < (p.K >> 2); k4 += NT) {   // 1 + scale, shift
+            const f32x4 sc = ((const f32x4*)p.ln_scale)[k4];
+            ((f32x4*)ss)[k4] = f32x4{1.0f + sc[0], 1.0f + sc[1], 1.0f + sc[2], 1.0f + sc[3]};
+            ((f32x4*)(ss + p.K))[k4] = ((const f32x4*)p.ln_shift)[k4];
+        }
+        if constexpr (EPI == E_QKV) {
+            if (tid < BM) {
+                const int row = min(m0 + tid, p.M - 1), bp = row / (2 * p.n), f = row % p.n, c = row / p.n - 2 * bp;
+                const int b = p.b0 + bp;
+                ro[tid] = RowOut{((((int64_t)bp * 2 + c) * p.heads) * p.Fq + f) * 64,
+                                 (int64_t)b * p.carry.stream_stride + (int64_t)(c * 2 * p.heads) * p.carry.Fr * 64,
+                                 own_base(p.carry, p.prompt, b) + f, 0};
             }
         }
-        if (kc + 1 < nk) lstore(buf ^ 1);
-        __syncthreads();
+        // NT / 16 rows at a time, 16 threads (one DPP row) per row: thread q takes
+        // the row's 4-column vectors q, q + 16, ...; the next rows load
+        // meanwhile.  Not unrolled: the code runs once per block, and its
+        // instruction fetches cost more than the loop.
+        constexpr int NV = 8;                          // K <= 512
+        constexpr int NP = (BM + NT / 16 - 1) / (NT / 16);   // passes
+        const int q = tid & 15, nv = p.K >> 6;
+        const float rK = 1.0f / (float)p.K;
+        f32x4 x[NV], nx[NV];
+        auto hload = [&](int mb, f32x4 (&v)[NV]) {
+            const f32x4* hr = (const f32x4*)(p.ln_h + (size_t)min(m0 + mb * (NT / 16) + min(tid >> 4, BM - 1), p.M - 1) * p.K) + q;
+#pragma unroll
+            for (int i = 0; i < NV; i++) v[i] = hr[16 * min(i, nv - 1)];
+        };
+        hload(0, x);
+        __syncthreads();                               // scale and shift are in place
+#pragma unroll 1
+        for (int mb = 0; mb < NP; mb++) {
+            hload(min(mb + 1, NP - 1), nx);
+            // the row's first value (lane 0 of the DPP row: row_newbcast:0)
+            const float x0 = row_ror<0x150>(x[0][0]);
+            float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+            for (int i = 0; i < NV; i++)
+                if (i < nv) {
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const float d = x[i][e] - x0;
+                        s1 += d;
+                        s2 = fmaf(d, d, s2);
+                    }
+                }
+            s1 = row_sum(s1);
+            s2 = row_sum(s2);
+            const float md = s1 * rK;
+            const float rstd = 1.0f / sqrtf(fmaxf(s2 * rK - md * md, 0.f) + 1e-6f), c0 = -(x0 + md) * rstd;
+            const int r = mb * (NT / 16) + (tid >> 4);
+            T* row = As + (size_t)r * LD;
+            if (r < BM) {
+#pragma unroll
+            for (int i = 0; i < NV; i++)
+                if (i < nv) {
+                    const int k = 4 * (q + 16 * i);
+                    const f32x4 sc = *(const f32x4*)(ss + k), sh = *(const f32x4*)(ss + p.K + k);
+                    f32x4 a;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) a[e] = fmaf(fmaf(x[i][e], rstd, c0), sc[e], sh[e]);
+                    store4<BF16>(row, k, a);
+                }
+            for (int k = p.K + 4 * q; k < p.KS * KQ; k += 64) store4<BF16>(row, k, f32x4{0.f, 0.f, 0.f, 0.f});
+            }
+#pragma unroll
+            for (int i = 0; i < NV; i++) x[i] = nx[i];
+        }
+    } else {
+        gload(0);
+        lstore(0);
     }
+    __syncthreads();
 
-    // acc[i][j][r]: row m0 + wm*16 MB + 16 j + l16, column n0 + wn*16 NB + 16 i + 4 g + r
+    f32x4 acc[MB][NB];
+    auto clear = [&] {
 #pragma unroll
-    for (int i = 0; i < NB; i++) {
-        const int col = n0 + wn * 16 * NB + 16 * i + 4 * g;
-        if (col >= p.N) continue;
+        for (int i = 0; i < MB; i++)
 #pragma unroll
-        for (int j = 0; j < MB; j++) {
-            const int row = m0 + wm * 16 * MB + 16 * j + l16;
-            if (row < p.M) epilogue4<BF16, EPI>(p, row, col, acc[i][j], epi_prefetch<EPI>(p, row, col));
+            for (int j = 0; j < NB; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    // D steps from LDS column `a` of this lane; the weights of the D steps
+    // after them (wn) replace the ones that are done.  ROWS: the lane's four
+    // results are four rows of one column instead of four columns of one row
+    // (the operands change places).
+    auto steps = [&](auto rows_tag, const T* a) {
+        constexpr bool ROWS = decltype(rows_tag)::value;
+        Frag x[2][MB];
+#pragma unroll
+        for (int i = 0; i < MB; i++) x[0][i] = *(const Frag*)(a + (size_t)16 * i * LD);
+#pragma unroll
+        for (int s = 0; s < D; s++) {
+            if (s + 1 < D) {
+#pragma unroll
+                for (int i = 0; i < MB; i++) x[(s + 1) & 1][i] = *(const Frag*)(a + (size_t)16 * i * LD + (s + 1) * KQ);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < (BF16 ? 1 : 4); u++)
+#pragma unroll
+                for (int j = 0; j < NB; j++)
+#pragma unroll
+                    for (int i = 0; i < MB; i++) {
+                        const Frag wf = __builtin_bit_cast(Frag, w[s][j]), xf = x[s & 1][i];
+                        if constexpr (BF16)
+                            acc[i][j] = ROWS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, wf, acc[i][j], 0, 0, 0)
+                                             : __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf, acc[i][j], 0, 0, 0);
+                        else
+                            acc[i][j] = ROWS ? __builtin_amdgcn_mfma_f32_16x16x4f32(xf[u], wf[u], acc[i][j], 0, 0, 0)
+                                             : __builtin_amdgcn_mfma_f32_16x16x4f32(wf[u], xf[u], acc[i][j], 0, 0, 0);
+                    }
+            load_w(s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    const T* a_lane = As + (size_t)l16 * LD + VE * g;
+    auto ahead = [&](int ks) {   // aim at the D steps from ks of this group
+#pragma unroll
+        for (int j = 0; j < NB; j++) wn[j] += ks * 64;
+    };
+
+    if constexpr (LN) {
+        for (int grp = 0; grp < p.groups; grp++) {
+            const int cb = cb0 + grp * NC * NB;
+            clear();
+            auto run = [&](auto rows_tag) {
+                for (int ks = 0; ks < p.KS; ks += D) {
+                    if (ks + D < p.KS) ahead(D);
+                    else aim(grp + 1 < p.groups ? grp + 1 : grp);   // the next group's first steps
+                    steps(rows_tag, a_lane + ks * KQ);
+                }
+            };
+            // values are stored transposed: their lanes take four frames of one dimension
+            const bool vcols = EPI == E_QKV && cb * 16 >= 2 * p.dim;
+            if (EPI == E_QKV && vcols) run(std::true_type{});
+            else run(std::false_type{});
+            if (cb >= N16) break;
+            if constexpr (EPI == E_QKV) {
+                // the group's columns lie in one head (dim and 16 NB divide by 64 and into it)
+                const int col0 = cb * 16, part = col0 / p.dim, hd = (col0 - part * p.dim) >> 6, d0 = col0 & 63;
+                const int64_t head_off = (int64_t)((part - 1) * p.heads + hd) * p.carry.Fr * 64;
+                if (!vcols) {
+                    f32x4 bias[NB];
+#pragma unroll
+                    for (int j = 0; j < NB; j++) bias[j] = *(const f32x4*)(p.bias + col0 + 16 * j + 4 * g);
+#pragma unroll
+                    for (int i = 0; i < MB; i++) {
+                        if (m0 + 16 * i + l16 >= p.M) continue;
+                        const RowOut r = ro[16 * i + l16];
+                        T* dst = part == 0 ? (T*)p.q + r.q + (int64_t)hd * p.Fq * 64
+                                           : (T*)p.carry.base + r.kv + head_off + (int64_t)r.frame * 64;
+#pragma unroll
+                        for (int j = 0; j < NB; j++) store4<BF16>(dst, d0 + 16 * j + 4 * g, acc[i][j] + bias[j]);
+                    }
+                } else {
+                    float bias[NB];
+#pragma unroll
+                    for (int j = 0; j < NB; j++) bias[j] = p.bias[col0 + 16 * j + l16];
+#pragma unroll
+                    for (int i = 0; i < MB; i++) {
+                        const int r0 = 16 * i + 4 * g;
+                        // n a multiple of 4: the four rows are four frames of one stream
+                        // and branch from a multiple of 4 (the regions start at one too)
+                        if ((p.n & 3) == 0) {
+                            if (m0 + r0 >= p.M) continue;
+                            const RowOut r = ro[r0];
+                            T* dst = (T*)p.carry.base + r.kv + head_off + (int64_t)(d0 + l16) * p.carry.Fr + r.frame;
+#pragma unroll
+                            for (int j = 0; j < NB; j++) {
+                                const float bj = bias[j];
+                                store4<BF16>(dst, (size_t)(16 * j) * p.carry.Fr, acc[i][j] + f32x4{bj, bj, bj, bj});
+                            }
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; e++) {
+                                if (m0 + r0 + e >= p.M) continue;
+                                const RowOut r = ro[r0 + e];
+                                T* dst = (T*)p.carry.base + r.kv + head_off + (int64_t)(d0 + l16) * p.carry.Fr + r.frame;
+#pragma unroll
+                                for (int j = 0; j < NB; j++)
+                                    store1<BF16>(dst, (size_t)(16 * j) * p.carry.Fr, acc[i][j][e] + bias[j]);
+                            }
+                        }
+                    }
+                }
+            } else {
+                // columns past N: clamped loads, nothing stored
+                f32x4 bias[NB];
+#pragma unroll
+                for (int j = 0; j < NB; j++) bias[j] = *(const f32x4*)(p.bias + min((cb + j) * 16 + 4 * g, p.N - 4));
+#pragma unroll
+                for (int i = 0; i < MB; i++) {
+                    if (m0 + 16 * i + l16 >= p.M) continue;
+                    const size_t at = (size_t)(m0 + 16 * i + l16) * p.N + cb * 16 + 4 * g;
+#pragma unroll
+                    for (int j = 0; j < NB; j++) {
+                        if ((cb + j) * 16 + 4 * g >= p.N) continue;
+                        f32x4 y = acc[i][j] + bias[j];
+                        if constexpr (EPI == E_GELU) {
+#pragma unroll
+                            for (int e = 0; e < 4; e++) y[e] = gelu_tanh<BF16>(y[e]);
+                            store4<BF16>(p.out, at + 16 * j, y);
+                        } else {
+                            store4<false>(p.out, at + 16 * j, y);
+                        }
+                    }
+                }
+            }
+        }
+    } else {
+        clear();
+        const int nc = p.KS / kChunk;
+        for (int c = 0; c < nc; c++) {
+            if (c + 1 < nc) gload(c + 1);
+            const T* a = a_lane + (size_t)(c & 1) * BM * LD + kw * kStepPad * KQ;
+#pragma unroll
+            for (int ks = 0; ks < kStepPad; ks += D) {
+                if (ks + D < kStepPad) ahead(D);
+                else if (c + 1 < nc) ahead(D + kChunk - kStepPad);
+                steps(std::false_type{}, a + ks * KQ);
+            }
+            if (c + 1 < nc) lstore((c + 1) & 1);
+            __syncthreads();
+        }
+        if constexpr (KW > 1) {   // (the chunks are done with)
+            f32x4* red = (f32x4*)smem;                 // [KW - 1][NC][MB * NB][64 lanes]
+            if (kw > 0) {
+#pragma unroll
+                for (int i = 0; i < MB; i++)
+#pragma unroll
+                    for (int j = 0; j < NB; j++) red[((wave - NC) * MB * NB + i * NB + j) * 64 + lane] = acc[i][j];
+            }
+            __syncthreads();
+            if (kw > 0) return;
+#pragma unroll
+            for (int w = 1; w < KW; w++)
+#pragma unroll
+                for (int i = 0; i < MB; i++)
+#pragma unroll
+                    for (int j = 0; j < NB; j++) acc[i][j] += red[(((w - 1) * NC + wave) * MB * NB + i * NB + j) * 64 + lane];
+        }
+#pragma unroll
+        for (int j = 0; j < NB; j++) {
+            const int col = (cb0 + j) * 16 + 4 * g;
+            if (col >= p.N) continue;
+            EpiPre e[MB];
+#pragma unroll
+            for (int i = 0; i < MB; i++) e[i] = epi_prefetch<EPI>(p, min(m0 + 16 * i + l16, p.M - 1), col);
+#pragma unroll
+            for (int i = 0; i < MB; i++) {
+                const int row = m0 + 16 * i + l16;
+                if (row < p.M) epilogue4<BF16, EPI>(p, row, col, acc[i][j], e[i]);
+            }
         }
     }
-}
-
-template <bool BF16, int MB, int NB>
-constexpr size_t tiled_lds_bytes()
-{
-    constexpr int KC = (MB * NB <= 4 ? 128 : 64) / (BF16 ? 1 : 2);
-    return (size_t)2 * (32 * MB + 32 * NB) * (KC + (BF16 ? 8 : 4)) * (BF16 ? 2 : 4);
 }
 
 // A kernel launched with more than 64 KB of dynamic LDS needs its limit
@@ -312,6 +560,10 @@ constexpr size_t tiled_lds_bytes()
 // largest size already allowed for that kernel (a race between two threads
 // only repeats the call).
 constexpr int kMaxDevices = 64;
+// Blocks that a LayerNorm GEMM keeps when it gives a block more column groups:
+// about two per CU (QKV and MLP up at 14,336 rows: 44.3 and 51.7 us; 59.1 and
+// 72.5 from 224 blocks, 56.9 and 64.9 from 900).
+constexpr int kGroupBlocks = 448;
 static hipError_t allow_lds(const void* kernel, size_t lds, size_t (&set)[kMaxDevices])
 {
     if (lds <= 64 * 1024) return hipSuccess;
@@ -326,21 +578,33 @@ static hipError_t allow_lds(const void* kernel, size_t lds, size_t (&set)[kMaxDe
 }
 
 template <bool BF16, int EPI, int MB, int NB>
-hipError_t launch_tiled(const GemmParams& p, hipStream_t st)
+hipError_t launch_tiled(GemmParams p, hipStream_t st)
 {
-    constexpr size_t lds = tiled_lds_bytes<BF16, MB, NB>();
+    constexpr bool LN = ln_operand<EPI>();
+    constexpr int KW = LN ? 1 : gemm_ksplit<MB, NB>(), NC = gemm_waves<MB, NB>() / KW;
+    if (!LN && p.KS % (KW * kStepPad) != 0) return hipErrorInvalidValue;
+    const size_t rows = (size_t)16 * MB * panel_row<BF16, LN, KW>(p.KS) * (BF16 ? 2 : 4);
+    const size_t lds = LN ? rows + (size_t)8 * p.K + (EPI == E_QKV ? 16 * MB * sizeof(RowOut) : 0) : 2 * rows;
+    static_assert((size_t)(KW - 1) * NC * MB * NB * 1024 <= (size_t)2 * 16 * MB * KW * kStepPad * 32, "partial sums fit the chunks");
+    const int tiles_m = (p.M + 16 * MB - 1) / (16 * MB), tiles_n = (p.N + 16 * NC * NB - 1) / (16 * NC * NB);
+    // a LayerNorm operand: one block per row tile normalises once for all its
+    // column groups, as long as that leaves kGroupBlocks blocks
+    p.nsplit = tiles_n;
+    if (LN)
+        while (p.nsplit > 1 && tiles_m * (p.nsplit - 1) >= kGroupBlocks) p.nsplit--;
+    p.groups = (tiles_n + p.nsplit - 1) / p.nsplit;
+    p.nsplit = (tiles_n + p.groups - 1) / p.groups;
     static size_t set[kMaxDevices] = {};
     const hipError_t e = allow_lds(reinterpret_cast<const void*>(&gemm_kernel<BF16, EPI, MB, NB>), lds, set);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gemm_kernel<BF16, EPI, MB, NB>), dim3((p.N + 32 * NB - 1) / (32 * NB), (p.M + 32 * MB - 1) / (32 * MB)),
-                       dim3(256), lds, st, p);
+    hipLaunchKernelGGL((gemm_kernel<BF16, EPI, MB, NB>), dim3(tiles_m * p.nsplit), dim3(64 * gemm_waves<MB, NB>()), lds, st, p);
     return hipGetLastError();
 }
 
 // Tile size by the number of 64 x 64 tiles the call would have: at least
-// DCF_TILE_BIG_BLOCKS -> 128 x 128, at least DCF_TILE_MID_BLOCKS -> 128 rows x
-// 64 columns, fewer -> 32 x 32 (more blocks for calls that would not fill the
-// machine).
+// DCF_TILE_BIG_BLOCKS -> 64 rows x 256 columns, at least DCF_TILE_MID_BLOCKS ->
+// 64 x 256 by 8 waves, fewer -> 16 x 128, or for K >= 1024 32 x 128 with two K
+// partitions (more blocks for calls that would not fill the machine).
 #ifndef DCF_TILE_BIG_BLOCKS
 #define DCF_TILE_BIG_BLOCKS 1024
 #endif
@@ -354,6 +618,7 @@ hipError_t launch_tiled_any(const GemmParams& p, hipStream_t st)
     const long small_blocks = (long)((p.N + 63) / 64) * ((p.M + 63) / 64);
     if (small_blocks >= DCF_TILE_BIG_BLOCKS) return launch_tiled<BF16, EPI, 4, 4>(p, st);
     if (small_blocks >= DCF_TILE_MID_BLOCKS) return launch_tiled<BF16, EPI, 4, 2>(p, st);
+    if (!ln_operand<EPI>() && p.K >= kSkinnyBigK && p.KS % (2 * kStepPad) == 0) return launch_tiled<BF16, EPI, 2, 2>(p, st);
     return launch_tiled<BF16, EPI, 1, 1>(p, st);
 }
 
@@ -385,20 +650,19 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmParams p)
     const int m0 = blockIdx.y * 16 * RB, n0 = blockIdx.x * 16 * NBLK;
     const int LDA = p.K + PAD;
     const T* A = (const T*)p.A;
-    const T* W = (const T*)p.W;
 
     const int ng = p.K / KQ;
     const int q0 = wave * ng / NW, q1 = (wave + 1) * ng / NW;
-    int col[NBLK];
+    const u32x4* W[NBLK];   // this lane's fragments of each column block (packed: one per K step)
 #pragma unroll
-    for (int j = 0; j < NBLK; j++) col[j] = min(n0 + 16 * j + l16, p.N - 1);
+    for (int j = 0; j < NBLK; j++) W[j] = (const u32x4*)p.W + (size_t)min(n0 / 16 + j, (p.N - 1) / 16) * p.KS * 64 + lane;
     // the first batch's weight fragments (they do not wait for the LayerNorm)
     u32x4 wf[BATCH][NBLK];
 #pragma unroll
     for (int b = 0; b < BATCH; b++)
 #pragma unroll
         for (int j = 0; j < NBLK; j++)
-            wf[b][j] = *(const u32x4*)(W + (size_t)col[j] * p.K + min(q0 + b, max(q1 - 1, 0)) * KQ + (BF16 ? 8 : 4) * g);
+            wf[b][j] = W[j][min(q0 + b, max(q1 - 1, 0)) * 64];
     // the epilogue's operands of the tiles this wave finalises
     EpiPre pre[PPW];
 #pragma unroll
@@ -450,7 +714,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmParams p)
             for (int b = 0; b < BATCH; b++)
 #pragma unroll
                 for (int j = 0; j < NBLK; j++)
-                    wf[b][j] = *(const u32x4*)(W + (size_t)col[j] * p.K + min(q + b, q1 - 1) * KQ + (BF16 ? 8 : 4) * g);
+                    wf[b][j] = W[j][min(q + b, q1 - 1) * 64];
         }
 #pragma unroll
         for (int b = 0; b < BATCH; b++) {
@@ -505,48 +769,6 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmParams p)
     }
 }
 
-// ------------------------------------------------------- modulated LayerNorm
-//
-// For calls of many rows: out = LN(h) * (1 + scale) + shift, one wave per
-// row, the row's values in registers (dim <= 512), mean and variance from
-// sums shifted by the row's first value, eps 1e-6; the operand of the
-// following tiled GEMM.
-template <bool BF16>
-__global__ __launch_bounds__(256) void lnmod_kernel(const float* h, void* out, const float* shift, const float* scale,
-                                                    int M, int dim)
-{
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= M) return;
-    const int nv = dim >> 6;
-    const float* hr = h + (size_t)row * dim;
-    float v[8], sc[8], sh[8];
-#pragma unroll
-    for (int k = 0; k < 8; k++) {
-        const int col = lane + 64 * min(k, nv - 1);
-        v[k] = hr[col];
-        sc[k] = scale[col];
-        sh[k] = shift[col];
-    }
-    const float x0 = __shfl(v[0], 0, 64);
-    float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; k++) {
-        const float d = (v[k] - x0) * (k < nv ? 1.0f : 0.0f);
-        s1 += d;
-        s2 += d * d;
-    }
-    s1 = wave_sum(s1);
-    s2 = wave_sum(s2);
-    const float md = s1 / (float)dim;
-    const float mean = x0 + md;
-    const float rs = 1.0f / sqrtf(fmaxf(s2 / (float)dim - md * md, 0.f) + 1e-6f);
-#pragma unroll
-    for (int k = 0; k < 8; k++)
-        if (k < nv) store1<BF16>(out, (size_t)row * dim + lane + 64 * k, (v[k] - mean) * rs * (1.0f + sc[k]) + sh[k]);
-}
-
-
 // Skinny shapes: waves and 16-column blocks per block, by operand kind.
 #ifndef DCF_SK_LN_NBLK
 #define DCF_SK_LN_NBLK 2
@@ -570,7 +792,6 @@ __global__ __launch_bounds__(256) void lnmod_kernel(const float* h, void* out, c
 #ifndef DCF_SK_PLAIN_RB
 #define DCF_SK_PLAIN_RB 1
 #endif
-constexpr int kSkinnyBigK = 1024;   // K from which the plain skinny GEMM uses DCF_SK_BIGK_WAVES waves
 
 size_t skinny_lds_bytes(const GemmParams& p, int bf16, int nw, int nblk, int rb)
 {
@@ -609,15 +830,6 @@ hipError_t launch_one(const GemmParams& p, hipStream_t st)
             return launch_skinny<BF16, EPI, false, DCF_SK_BIGK_WAVES, DCF_SK_PLAIN_NBLK, DCF_SK_PLAIN_RB>(p, st);
         else
             return launch_skinny<BF16, EPI, false, DCF_SK_PLAIN_WAVES, DCF_SK_PLAIN_NBLK, DCF_SK_PLAIN_RB>(p, st);
-    } else if (LN) {
-        // the normalised operand is written once to p.A by its own launch
-        hipLaunchKernelGGL((lnmod_kernel<BF16>), dim3((p.M + 3) / 4), dim3(256), 0, st, p.ln_h, const_cast<void*>(p.A),
-                           p.ln_shift, p.ln_scale, p.M, p.K);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        GemmParams q = p;
-        q.ln_h = nullptr;
-        return launch_tiled_any<BF16, EPI>(q, st);
     }
     return launch_tiled_any<BF16, EPI>(p, st);
 }
@@ -627,12 +839,11 @@ hipError_t launch_gemm(const GemmParams& p, int epi, int bf16, hipStream_t st)
     const bool ln = p.ln_h != nullptr;
 #define DCF_GEMM(B, E, L)                                     \
     if (bf16 == B && epi == E && ln == L) return launch_one<B, E, L>(p, st);
-    // the LayerNorm operand exists for the GEMMs that follow one; every
-    // GEMM can take a plain operand
-    DCF_GEMM(1, E_H, false) DCF_GEMM(1, E_QKV, true) DCF_GEMM(1, E_QKV, false) DCF_GEMM(1, E_RES, false)
-    DCF_GEMM(1, E_GELU, true) DCF_GEMM(1, E_GELU, false) DCF_GEMM(1, E_VEL, true) DCF_GEMM(1, E_VEL, false)
-    DCF_GEMM(0, E_H, false) DCF_GEMM(0, E_QKV, true) DCF_GEMM(0, E_QKV, false) DCF_GEMM(0, E_RES, false)
-    DCF_GEMM(0, E_GELU, true) DCF_GEMM(0, E_GELU, false) DCF_GEMM(0, E_VEL, true) DCF_GEMM(0, E_VEL, false)
+    // the LayerNorm operand exists for exactly the GEMMs that follow one
+    DCF_GEMM(1, E_H, false) DCF_GEMM(1, E_QKV, true) DCF_GEMM(1, E_RES, false) DCF_GEMM(1, E_GELU, true)
+    DCF_GEMM(1, E_VEL, true)
+    DCF_GEMM(0, E_H, false) DCF_GEMM(0, E_QKV, true) DCF_GEMM(0, E_RES, false) DCF_GEMM(0, E_GELU, true)
+    DCF_GEMM(0, E_VEL, true)
 #undef DCF_GEMM
     return hipErrorInvalidValue;
 }
@@ -695,9 +906,9 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(const AttnParams p)
     int sb[kMaxSegments], sl[kMaxSegments], st0[kMaxSegments + 1], ns = 0;
     if (!p.prompt) {
         const int64_t hist = cr.hist[b];
-        const int nh = hist < cr.R ? (int)hist : cr.R;
+        const int nh = hist < cr.R ? (int)hist : cr.R, cur = cr.slot[b];
         for (int r = 0; r < nh; r++) {
-            sb[ns] = cr.Pr + (int)((hist - 1 - r) % (cr.R + 1)) * cr.Sl;
+            sb[ns] = cr.Pr + (cur > r ? cur - 1 - r : cur - r + cr.R) * cr.Sl;
             sl[ns++] = p.f_chunk;
         }
         sb[ns] = 0;
@@ -799,14 +1010,14 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(const AttnParams p)
         mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
         mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
         const float mn = fmaxf(m, mt);
-        const float alpha = exp2f(m - mn);
+        const float alpha = __builtin_amdgcn_exp2f(m - mn);
         m = mn;
         float ps = 0.f;
 #pragma unroll
         for (int j = 0; j < 2; j++)
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                st[j][r] = exp2f(st[j][r] - mn);
+                st[j][r] = __builtin_amdgcn_exp2f(st[j][r] - mn);
                 ps += st[j][r];
             }
         lsum = lsum * alpha + ps;
@@ -921,7 +1132,7 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(const AttnParams p)
     for (int db = 0; db < 4; db++) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < NW; w++) {
-        const float sc = exp2f(Ms[w * QB + qq] - mx);
+        const float sc = __builtin_amdgcn_exp2f(Ms[w * QB + qq] - mx);
         L += sc * Ls[w * QB + qq];
 #pragma unroll
         for (int db = 0; db < 4; db++) acc[db] += sc * *(const f32x4*)(Os + ((size_t)w * QB + qq) * kAttnLd + 16 * db + 4 * g);
@@ -1091,7 +1302,8 @@ hipError_t launch_consts(const ConstParams& p, hipStream_t st)
 
 // ------------------------------------------------------------ stream state
 
-__global__ void advance_kernel(int64_t* hist, int64_t* pos, int* plen, int mode, int b, int P, int B, int f_chunk)
+__global__ void advance_kernel(int64_t* hist, int64_t* pos, int* plen, int* slot, int mode, int b, int P, int B,
+                               int f_chunk, int R)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (mode == 0) {
@@ -1099,6 +1311,7 @@ __global__ void advance_kernel(int64_t* hist, int64_t* pos, int* plen, int mode,
             hist[b] = 0;
             pos[b] = 0;
             plen[b] = 0;
+            slot[b] = 0;
         }
     } else if (mode == 1) {
         if (t == 0) {
@@ -1108,14 +1321,15 @@ __global__ void advance_kernel(int64_t* hist, int64_t* pos, int* plen, int mode,
     } else if (t < B) {
         hist[t] += 1;
         pos[t] += f_chunk;
+        slot[t] = slot[t] == R ? 0 : slot[t] + 1;
     }
 }
 
-hipError_t launch_advance(int64_t* hist, int64_t* pos, int* plen, int mode, int b, int P, int B, int f_chunk,
-                          hipStream_t st)
+hipError_t launch_advance(int64_t* hist, int64_t* pos, int* plen, int* slot, int mode, int b, int P, int B,
+                          int f_chunk, int R, hipStream_t st)
 {
-    hipLaunchKernelGGL(advance_kernel, dim3((B + 255) / 256), dim3(256), 0, st, hist, pos, plen, mode, b, P, B,
-                       f_chunk);
+    hipLaunchKernelGGL(advance_kernel, dim3((B + 255) / 256), dim3(256), 0, st, hist, pos, plen, slot, mode, b, P, B,
+                       f_chunk, R);
     return hipGetLastError();
 }
 

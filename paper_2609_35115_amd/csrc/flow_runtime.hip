@@ -111,7 +111,7 @@ struct dc_flow_state {
     float *mods = nullptr, *fmods = nullptr, *t = nullptr, *dt = nullptr, *silu_temb = nullptr;
     // stream state
     int64_t *hist = nullptr, *pos = nullptr;
-    int* plen = nullptr;
+    int *plen = nullptr, *slot = nullptr;
     uint64_t* keys = nullptr;
     float* spk = nullptr;
     // carry
@@ -119,7 +119,7 @@ struct dc_flow_state {
     int Pr = 0, Sl = 0, R = 0, Fr = 0;
     int64_t stream_stride = 0;
     // per-call buffers
-    void *xin = nullptr, *a = nullptr, *o = nullptr, *u = nullptr, *q = nullptr;
+    void *xin = nullptr, *o = nullptr, *u = nullptr, *q = nullptr;
     float *h = nullptr, *v = nullptr, *x = nullptr;
     float *mu_in = nullptr, *mel_out = nullptr, *cond_in = nullptr, *gather = nullptr;
     hipGraph_t graph = nullptr;
@@ -157,6 +157,7 @@ CarryRef carry_ref(const dc_flow_state* s, int i, int l)
     r.Sl = s->Sl;
     r.R = s->R;
     r.hist = s->hist;
+    r.slot = s->slot;
     r.plen = s->plen;
     return r;
 }
@@ -242,7 +243,7 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.ln_shift = g.ln_scale = nullptr;
         };
         auto normed = [&](const float* shift, const float* scale) {   // A = LN(h) * (1 + scale) + shift
-            g.A = s->a;                                                // written there for calls of many rows
+            g.A = nullptr;
             g.ln_h = s->h;
             g.ln_shift = shift;
             g.ln_scale = scale;
@@ -253,6 +254,7 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
         g.bias = s->b_in;
         g.N = D;
         g.K = 4 * M;
+        g.KS = k_steps(4 * M, s->bf);
         g.h = s->h;
         gemm_cost("gemm:in", D, 4 * M, es, 4, false);
         DCF_TRY(launch_gemm(g, E_H, bf, st));
@@ -264,6 +266,8 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.bias = s->b_qkv[l];
             g.N = 3 * D;
             g.K = D;
+            g.KS = k_steps(D, s->bf);
+        g.KS = k_steps(D, s->bf);
             g.carry = cr;
             gemm_cost("gemm:qkv", 3 * D, D, 4, es, false);
             DCF_TRY(launch_gemm(g, E_QKV, bf, st));
@@ -277,6 +281,8 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.bias = s->b_o[l];
             g.N = D;
             g.K = D;
+            g.KS = k_steps(D, s->bf);
+        g.KS = k_steps(D, s->bf);
             g.gate = md + 2 * D;
             gemm_cost("gemm:o", D, D, es, 4, true);
             DCF_TRY(launch_gemm(g, E_RES, bf, st));
@@ -285,6 +291,8 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.bias = s->b_fc1[l];
             g.N = c.mlp;
             g.K = D;
+            g.KS = k_steps(D, s->bf);
+        g.KS = k_steps(D, s->bf);
             g.out = s->u;
             gemm_cost("gemm:fc1", c.mlp, D, 4, es, false);
             DCF_TRY(launch_gemm(g, E_GELU, bf, st));
@@ -293,6 +301,8 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.bias = s->b_fc2[l];
             g.N = D;
             g.K = c.mlp;
+            g.KS = k_steps(c.mlp, s->bf);
+        g.KS = k_steps(c.mlp, s->bf);
             g.gate = md + 5 * D;
             gemm_cost("gemm:fc2", D, c.mlp, es, 4, true);
             DCF_TRY(launch_gemm(g, E_RES, bf, st));
@@ -303,6 +313,7 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
         g.bias = s->b_out;
         g.N = M;
         g.K = D;
+        g.KS = k_steps(D, s->bf);
         g.out = s->v;
         gemm_cost("gemm:out", M, D, 4, 4, false);
         DCF_TRY(launch_gemm(g, E_VEL, bf, st));
@@ -312,7 +323,7 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
     }
     describe("advance", 0, 0, 0);
     if (!prompt && n >= c.f_chunk && !rec)
-        DCF_TRY(launch_advance(s->hist, s->pos, s->plen, 2, 0, 0, c.batch, c.f_chunk, st));
+        DCF_TRY(launch_advance(s->hist, s->pos, s->plen, s->slot, 2, 0, 0, c.batch, c.f_chunk, s->R, st));
 #undef DCF_TRY
     if (count) *count = k;
     return hipSuccess;
@@ -373,15 +384,16 @@ dc_status dc_flow_init(const void* weights_blob, size_t blob_bytes, const dc_flo
         return at;
     };
     const size_t es = s->esz;
-    const size_t o_win = place((size_t)D * 4 * M * es);
+    auto packed = [&](int N, int K) { return (size_t)((N + 15) / 16) * k_steps(K, s->bf) * 1024; };
+    const size_t o_win = place(packed(D, 4 * M));
     std::vector<size_t> o_wqkv(NL), o_wo(NL), o_wfc1(NL), o_wfc2(NL), o_bqkv(NL), o_bo(NL), o_bfc1(NL), o_bfc2(NL);
     for (int l = 0; l < NL; l++) {
-        o_wqkv[l] = place((size_t)3 * D * D * es);
-        o_wo[l] = place((size_t)D * D * es);
-        o_wfc1[l] = place((size_t)c.mlp * D * es);
-        o_wfc2[l] = place((size_t)D * c.mlp * es);
+        o_wqkv[l] = place(packed(3 * D, D));
+        o_wo[l] = place(packed(D, D));
+        o_wfc1[l] = place(packed(c.mlp, D));
+        o_wfc2[l] = place(packed(D, c.mlp));
     }
-    const size_t o_wout = place((size_t)M * D * es);
+    const size_t o_wout = place(packed(M, D));
     const size_t o_bin = place((size_t)D * 4);
     for (int l = 0; l < NL; l++) {
         o_bqkv[l] = place((size_t)3 * D * 4);
@@ -400,6 +412,7 @@ dc_status dc_flow_init(const void* weights_blob, size_t blob_bytes, const dc_flo
     const size_t o_hist = place((size_t)B * 8);
     const size_t o_pos = place((size_t)B * 8);
     const size_t o_plen = place((size_t)B * 4);
+    const size_t o_slot = place((size_t)B * 4);
     const size_t o_keys = place((size_t)B * 8);
     const size_t o_spk = place((size_t)B * M * 4);
     const size_t o_carry = place((size_t)B * s->stream_stride * es);
@@ -410,7 +423,6 @@ dc_status dc_flow_init(const void* weights_blob, size_t blob_bytes, const dc_flo
                                     (size_t)2 * c.heads * round_up(c.f_prompt, 64) * 64);
     const size_t o_xin = place((size_t)rows_max * 4 * M * es);
     const size_t o_h = place((size_t)rows_max * D * 4);
-    const size_t o_a = place((size_t)rows_max * D * es);
     const size_t o_o = place((size_t)rows_max * D * es);
     const size_t o_u = place((size_t)rows_max * c.mlp * es);
     const size_t o_q = place(q_elems * es);
@@ -462,12 +474,12 @@ dc_status dc_flow_init(const void* weights_blob, size_t blob_bytes, const dc_flo
     s->hist = (int64_t*)(A + o_hist);
     s->pos = (int64_t*)(A + o_pos);
     s->plen = (int*)(A + o_plen);
+    s->slot = (int*)(A + o_slot);
     s->keys = (uint64_t*)(A + o_keys);
     s->spk = (float*)(A + o_spk);
     s->carry = A + o_carry;
     s->xin = A + o_xin;
     s->h = (float*)(A + o_h);
-    s->a = A + o_a;
     s->o = A + o_o;
     s->u = A + o_u;
     s->q = A + o_q;
@@ -481,33 +493,41 @@ dc_status dc_flow_init(const void* weights_blob, size_t blob_bytes, const dc_flo
     // host image of the weight region: the per-step Linear weights in the
     // operand type (round to nearest even for bf16), biases in fp32
     std::vector<char> host(weights_end, 0);
-    auto put_w = [&](size_t at, int64_t src, size_t n) {
-        if (s->bf) {
-            uint16_t* d = (uint16_t*)(host.data() + at);
-            for (size_t i = 0; i < n; i++) {
-                uint32_t u;
-                std::memcpy(&u, blob + src + i, 4);
-                if ((u & 0x7f800000u) == 0x7f800000u) d[i] = (uint16_t)((u >> 16) | ((u & 0x007fffffu) ? 0x40u : 0u));
-                else d[i] = (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+    auto put_w = [&](size_t at, int64_t src, int N, int K) {
+        const int kv = s->bf ? 8 : 4, ks = k_steps(K, s->bf);   // K values of a lane's fragment, steps
+        for (int n = 0; n < N; n++) {
+            const float* row = blob + src + (int64_t)n * K;
+            char* blk = host.data() + at + (size_t)(n / 16) * ks * 1024 + (size_t)(n % 16) * 16;
+            for (int k = 0; k < K; k += kv) {   // K is a multiple of 16: whole fragments
+                char* d = blk + (size_t)(k / (4 * kv)) * 1024 + (size_t)(k / kv % 4) * 256;
+                if (s->bf)
+                    for (int e = 0; e < 8; e++) {
+                        uint32_t u;
+                        std::memcpy(&u, row + k + e, 4);
+                        const uint16_t h = (u & 0x7f800000u) == 0x7f800000u
+                                               ? (uint16_t)((u >> 16) | ((u & 0x007fffffu) ? 0x40u : 0u))
+                                               : (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+                        std::memcpy(d + 2 * e, &h, 2);
+                    }
+                else
+                    std::memcpy(d, row + k, 16);
             }
-        } else {
-            std::memcpy(host.data() + at, blob + src, n * 4);
         }
     };
     auto put_b = [&](size_t at, int64_t src, size_t n) { std::memcpy(host.data() + at, blob + src, n * 4); };
-    put_w(o_win, bm.inW, (size_t)D * 4 * M);
+    put_w(o_win, bm.inW, D, 4 * M);
     put_b(o_bin, bm.inb, D);
     for (int l = 0; l < NL; l++) {
-        put_w(o_wqkv[l], bm.qkvW[l], (size_t)3 * D * D);
+        put_w(o_wqkv[l], bm.qkvW[l], 3 * D, D);
         put_b(o_bqkv[l], bm.qkvb[l], (size_t)3 * D);
-        put_w(o_wo[l], bm.oW[l], (size_t)D * D);
+        put_w(o_wo[l], bm.oW[l], D, D);
         put_b(o_bo[l], bm.ob[l], D);
-        put_w(o_wfc1[l], bm.fc1W[l], (size_t)c.mlp * D);
+        put_w(o_wfc1[l], bm.fc1W[l], c.mlp, D);
         put_b(o_bfc1[l], bm.fc1b[l], c.mlp);
-        put_w(o_wfc2[l], bm.fc2W[l], (size_t)D * c.mlp);
+        put_w(o_wfc2[l], bm.fc2W[l], D, c.mlp);
         put_b(o_bfc2[l], bm.fc2b[l], D);
     }
-    put_w(o_wout, bm.outW, (size_t)M * D);
+    put_w(o_wout, bm.outW, M, D);
     put_b(o_bout, bm.outb, M);
     e = hipMemcpy(A, host.data(), weights_end, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemsetAsync(A + weights_end, 0, s->arena_bytes - weights_end, s->stream);
@@ -587,10 +607,10 @@ dc_status dc_flow_prompt(dc_flow_state* s, int32_t b, const float* mu, const flo
     hipError_t e = hipMemcpyAsync(s->mu_in, mu, fb, k, s->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(s->cond_in, cond, fb, k, s->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(s->spk + (size_t)b * c.n_mel, spk, (size_t)c.n_mel * 4, k, s->stream);
-    if (e == hipSuccess) e = launch_advance(s->hist, s->pos, s->plen, 0, b, frames, c.batch, c.f_chunk, s->stream);
+    if (e == hipSuccess) e = launch_advance(s->hist, s->pos, s->plen, s->slot, 0, b, frames, c.batch, c.f_chunk, s->R, s->stream);
     // the prompt frames' own solution is not an output
     if (e == hipSuccess) e = enqueue_call(s, b, 1, frames, 1, s->mu_in, s->cond_in, nullptr, s->stream, nullptr);
-    if (e == hipSuccess) e = launch_advance(s->hist, s->pos, s->plen, 1, b, frames, c.batch, c.f_chunk, s->stream);
+    if (e == hipSuccess) e = launch_advance(s->hist, s->pos, s->plen, s->slot, 1, b, frames, c.batch, c.f_chunk, s->R, s->stream);
     if (e != hipSuccess) return device_fail(s, e, "prompt pass");
     s->plen_host[b] = frames;
     s->hist_host[b] = 0;

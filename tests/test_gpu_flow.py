@@ -294,6 +294,29 @@ def test_many_rows_take_the_tiled_path_and_match_oracle(dtype):
     dec.close()
 
 
+@pytest.mark.parametrize("dtype,dim,mlp,f_call,B", [
+    ("bf16", 64, 1056, 13, 24),    # K = 64 padded to 8 steps; n not a multiple of 4; K >= 1024 of an odd chunk count
+    ("f32", 64, 1056, 13, 24),
+    ("bf16", 192, 2048, 12, 27),   # a ragged last row tile; K = 2048 in two partitions; heads that straddle column groups
+    ("f32", 192, 2048, 11, 27),
+    ("bf16", 512, 1024, 13, 160),  # 4,160 rows: the widest tiles, several column groups per block
+    ("f32", 512, 1024, 8, 260),
+])
+def test_tiled_gemm_edges_match_oracle(dtype, dim, mlp, f_call, B):
+    """Calls of more than 512 rows at the tiled GEMM's edges, against the oracle."""
+    a = dict(TINY, dim=dim, heads=dim // 64, mlp=mlp, n_mel=24, depth=1, n_steps=2, f_prompt=9, f_retained=8,
+             f_chunk=8, f_call=f_call)
+    blob = synth.make_flow_weights(a, 8)
+    calls = [f_call, f_call]
+    dec, outs, mu, prompts = _run_gpu(a, dtype, blob, B, a["f_prompt"], calls)
+    for b in (0, B // 2, B - 1):
+        _s, ref = _run_oracle(a, dtype, blob, b, prompts[b], mu[b], calls)
+        for k, (g, r) in enumerate(zip(outs, ref)):
+            e, _ = err_stats(g[b], r)
+            assert e <= TOL[dtype], f"stream {b} call {k}: {e:.3e}"
+    dec.close()
+
+
 def test_real_shape_batch20_every_tile_size():
     """20 paper-shaped streams in bf16: 2,240 rows per call, so the MLP-up GEMM
     takes 128 x 128 tiles, the input, QKV, attention-output and MLP-down GEMMs
