@@ -87,6 +87,7 @@ struct AttnParams {
     void* o;                 // [M][dim] operand type
     int prompt;              // 1: the keys are the call's own frames only
     int n, b0, heads, dim, f_chunk;
+    int max_tiles;           // 32-key tiles that a stream's keys can come to
 };
 
 struct AssembleParams {

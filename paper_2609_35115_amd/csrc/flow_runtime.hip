@@ -271,7 +271,8 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.carry = cr;
             gemm_cost("gemm:qkv", 3 * D, D, 4, es, false);
             DCF_TRY(launch_gemm(g, E_QKV, bf, st));
-            AttnParams at{s->q, Fq, cr, s->o, prompt, n, b0, c.heads, D, c.f_chunk};
+            AttnParams at{s->q, Fq, cr, s->o, prompt, n, b0, c.heads, D, c.f_chunk,
+                          s->R * ((c.f_chunk + 31) / 32) + (c.f_prompt + 31) / 32 + (n + 31) / 32};
             // per (stream, branch, head): n queries x its keys x 64, twice (scores, values)
             describe("attn", 4.0 * 2 * c.heads * 64 * (double)n * ext_keys,
                      2.0 * 2 * c.heads * 64 * (double)ext_keys * es + 2.0 * rows * D * es, 1);
@@ -368,10 +369,10 @@ dc_status dc_flow_init(const void* weights_blob, size_t blob_bytes, const dc_flo
     s->plen_host.assign(B, 0);   // no stream has a turn
     s->hist_host.assign(B, 0);
 
-    // carry geometry: prompt region and slots padded to 4 frames (aligned
-    // 4-key value groups), R history slots plus the one a call writes
-    s->Pr = round_up(c.f_prompt, 4);
-    s->Sl = round_up(c.f_call, 4);
+    // carry geometry: prompt region and slots padded to 8 frames (16-byte
+    // groups of values), R history slots plus the one a call writes
+    s->Pr = round_up(c.f_prompt, 8);
+    s->Sl = round_up(c.f_call, 8);
     s->R = c.f_retained / c.f_chunk;
     s->Fr = s->Pr + (s->R + 1) * s->Sl;
     s->stream_stride = (int64_t)NS * NL * 4 * c.heads * s->Fr * 64;

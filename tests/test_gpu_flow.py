@@ -317,6 +317,29 @@ def test_tiled_gemm_edges_match_oracle(dtype, dim, mlp, f_call, B):
     dec.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("f_prompt,f_chunk,f_call", [
+    (1, 1, 1),       # one key in a prompt, then two tiles of one key: half of the waves have none
+    (31, 8, 13),     # tiles cut short by one key, by many
+    (33, 40, 44),    # a key past a tile; chunks of two tiles; history after two calls
+    (64, 33, 70),    # whole tiles; two query blocks
+])
+def test_wide_attention_edges_match_oracle(dtype, f_prompt, f_chunk, f_call):
+    """64 (stream, branch, head) blocks take the wide attention: tile and query
+    edges against the oracle, with the retained chunks in every ring slot."""
+    a = dict(TINY, dim=64, heads=1, n_mel=8, depth=1, n_steps=2, f_prompt=f_prompt, f_retained=2 * f_chunk,
+             f_chunk=f_chunk, f_call=f_call)
+    blob = synth.make_flow_weights(a, 9)
+    B, calls = 32, [f_call] * 4
+    dec, outs, mu, prompts = _run_gpu(a, dtype, blob, B, f_prompt, calls)
+    for b in (0, 31):
+        _s, ref = _run_oracle(a, dtype, blob, b, prompts[b], mu[b], calls)
+        for k, (g, r) in enumerate(zip(outs, ref)):
+            e, _ = err_stats(g[b], r)
+            assert e <= TOL[dtype], f"stream {b} call {k}: {e:.3e}"
+    dec.close()
+
+
 def test_real_shape_batch20_every_tile_size():
     """20 paper-shaped streams in bf16: 2,240 rows per call, so the MLP-up GEMM
     takes 128 x 128 tiles, the input, QKV, attention-output and MLP-down GEMMs
