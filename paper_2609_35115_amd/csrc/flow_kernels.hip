@@ -914,13 +914,17 @@ struct AttnKeys {
 };
 
 // Maximum over the lanes that differ in bits 4 and 5 (the four groups of 16).
+// (The swaps' results go through scalars: a bit cast straight from a vector's
+// element 1 reads element 0.)
 __device__ __forceinline__ float max_xor16_32(float v)
 {
     const uint32_t u = __builtin_bit_cast(uint32_t, v);
     const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const uint32_t w = __builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, a[0]), __builtin_bit_cast(float, a[1])));
+    const uint32_t a0 = a[0], a1 = a[1];
+    const uint32_t w = __builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1)));
     const auto c = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-    return fmaxf(__builtin_bit_cast(float, c[0]), __builtin_bit_cast(float, c[1]));
+    const uint32_t c0 = c[0], c1 = c[1];
+    return fmaxf(__builtin_bit_cast(float, c0), __builtin_bit_cast(float, c1));
 }
 
 // Calls with enough (stream, branch, head) blocks to fill the device: a block

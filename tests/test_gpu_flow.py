@@ -340,6 +340,25 @@ def test_wide_attention_edges_match_oracle(dtype, f_prompt, f_chunk, f_call):
     dec.close()
 
 
+@pytest.mark.parametrize("B", [2, 32])   # the narrow and the wide attention
+def test_attention_scores_far_apart(B):
+    """Scores some hundreds apart (fp32; the query and key weights times 8): the
+    running maximum has to be every key's, or the exponentials overflow."""
+    a = dict(TINY, dim=64, heads=1, n_mel=8, depth=1, n_steps=2)
+    blob = synth.make_flow_weights(a, 10)
+    w = synth.split_flow_weights(a, blob)
+    w["b0.qkv.W"][:128] *= 8.0
+    calls = [a["f_call"]] * 3
+    dec, outs, mu, prompts = _run_gpu(a, "f32", blob, B, a["f_prompt"], calls)
+    for b in range(2):
+        _s, ref = _run_oracle(a, "f32", blob, b, prompts[b], mu[b], calls)
+        for k, (g, r) in enumerate(zip(outs, ref)):
+            # scores of order 64 carry fp32 roundings of order 64 * 2^-24 * sqrt(64) = 3e-5 into the softmax
+            e, _ = err_stats(g[b], r)
+            assert e <= TOL["f32"], f"stream {b} call {k}: {e:.3e}"
+    dec.close()
+
+
 def test_real_shape_batch20_every_tile_size():
     """20 paper-shaped streams in bf16: 2,240 rows per call, so the MLP-up GEMM
     takes 128 x 128 tiles, the input, QKV, attention-output and MLP-down GEMMs
