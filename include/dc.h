@@ -204,6 +204,26 @@ dc_status dc_decode_chunk(dc_state* s, const int32_t* tokens, int32_t n, float* 
 dc_status dc_decode_chunk_f0(dc_state* s, const int32_t* tokens, const float* f0, int32_t n, float* audio_out);
 
 /*
+ * The same call ordered on hip_stream (a hipStream_t; NULL: the default
+ * stream) instead of the state's own stream: f0 as for dc_decode_chunk_f0, or
+ * NULL for a decoder without a source; device pointers only (DC_EINVAL for a
+ * DC_HOST_PTRS state).  It comes after every earlier call of this state, and
+ * every later call of any kind after it.  A caller whose inputs and outputs
+ * live on its own stream so needs no event and no wait on it.  Other work that
+ * the caller itself puts on the state's stream comes after this call only once
+ * dc_settle (or any call that uses that stream) has been called.  The device
+ * of hip_stream has to be the state's.  Not while hip_stream is being captured
+ * (the state's own stream would join the capture).  Errors as
+ * dc_decode_chunk_f0.
+ */
+dc_status dc_decode_chunk_on(dc_state* s, void* hip_stream, const int32_t* tokens, const float* f0, int32_t n,
+                             float* audio_out);
+
+/* Order the state's own stream after every call made with dc_decode_chunk_on
+ * (asynchronous). */
+dc_status dc_settle(dc_state* s);
+
+/*
  * dc_decode_chunk_f0 for callers that cannot allocate device memory or must
  * not have the library do so on their behalf (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation): the call's one

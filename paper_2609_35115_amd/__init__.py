@@ -86,6 +86,8 @@ SIGNATURES = {
     "dc_decode_chunk": ([_P, _P, ctypes.c_int32, _P], ctypes.c_int),
     "dc_decode_chunk_f0": ([_P, _P, _P, ctypes.c_int32, _P], ctypes.c_int),
     "dc_decode_chunk_f0_static": ([_P, _P, _P, ctypes.c_int32, _P], ctypes.c_int),
+    "dc_decode_chunk_on": ([_P, _P, _P, _P, ctypes.c_int32, _P], ctypes.c_int),
+    "dc_settle": ([_P], ctypes.c_int),
     "dc_reset": ([_P], ctypes.c_int),
     "dc_reset_stream": ([_P, ctypes.c_int32], ctypes.c_int),
     "dc_sync": ([_P], ctypes.c_int),
@@ -208,6 +210,17 @@ def dc_decode_chunk_f0_static(h, tokens, f0, n: int, audio_out) -> int:
     return lib().dc_decode_chunk_f0_static(h, _ptr(tokens) if tokens is not None else None,
                                            _ptr(f0) if f0 is not None else None, n,
                                            _ptr(audio_out) if audio_out is not None else None)
+
+
+def dc_decode_chunk_on(h, stream: int, tokens, f0, n: int, audio_out) -> int:
+    """Raw call: returns the status (no exception).  stream: a hipStream_t (0: the default stream)."""
+    return lib().dc_decode_chunk_on(h, stream, _ptr(tokens) if tokens is not None else None,
+                                    _ptr(f0) if f0 is not None else None, n,
+                                    _ptr(audio_out) if audio_out is not None else None)
+
+
+def dc_settle(h) -> int:
+    return lib().dc_settle(h)
 
 
 def dc_reset(h) -> int:
@@ -371,8 +384,10 @@ def check_decode_args(tokens, f0, batch: int, max_tokens: int, fpt: int, has_sou
 
 
 class Decoder:
-    """One dc_state on the current GPU, with torch-ROCm tensors for device memory
-    and a dedicated torch stream that every call is ordered on."""
+    """One dc_state on the current GPU, with torch-ROCm tensors for device memory.
+    Decodes are ordered on the caller's current stream, as torch operations are;
+    the C calls on the handle run on the state's own stream (`stream`, a dedicated
+    torch stream), each after every decode before it."""
 
     def __init__(self, arch: dict, dtype: str, blob: np.ndarray, batch: int, chunk_tokens: int,
                  max_tokens: int | None = None, flags: int = 0, tile_variant: int = 0, rng_seed: int = 0):
@@ -380,14 +395,22 @@ class Decoder:
         self.torch = torch
         self.arch, self.dtype, self.batch = arch, dtype, batch
         self.host = bool(flags & DC_HOST_PTRS)
-        self.stream = torch.cuda.Stream()
+        self._stream = torch.cuda.Stream()
+        self.device = torch.cuda.current_device()
         self.cfg = make_cfg(arch, dtype, batch, chunk_tokens, max_tokens, flags, tile_variant,
-                            self.stream.cuda_stream, rng_seed)
+                            self._stream.cuda_stream, rng_seed)
         self.has_source = arch.get("n_harmonics", 0) > 0
         self.spt = dc_samples_per_token(self.cfg)
         self.chunk_tokens = chunk_tokens
         self.max_tokens = self.cfg.max_tokens
         self.h = dc_init(blob, self.cfg)
+
+    @property
+    def stream(self):
+        """The state's own stream, ordered after every decode so far."""
+        if self.h is not None:
+            dc_settle(self.h)
+        return self._stream
 
     def close(self):
         if self.h is not None:
@@ -419,6 +442,21 @@ class Decoder:
                 st = call(self.h, tok, np.ascontiguousarray(f0, dtype=np.float32), n, out)
             else:
                 st = dc_decode_chunk(self.h, tok, n, out)
+        elif not (static_scratch or torch.cuda.current_device() != self.device
+                  or torch.cuda.is_current_stream_capturing()):
+            # ordered on the caller's stream, as a torch operation is: no
+            # hand-over to the state's stream and back
+            if isinstance(tokens, np.ndarray):
+                tok = torch.from_numpy(np.ascontiguousarray(tokens, dtype=np.int32)).to("cuda")
+            else:
+                tok = tokens.contiguous()
+            f0d = f0
+            if isinstance(f0, np.ndarray):
+                f0d = torch.from_numpy(np.ascontiguousarray(f0, dtype=np.float32)).to("cuda")
+            elif f0 is not None:
+                f0d = f0.contiguous()
+            out = torch.empty((self.batch, n * self.spt), dtype=torch.float32, device="cuda")
+            st = dc_decode_chunk_on(self.h, torch.cuda.current_stream().cuda_stream, tok, f0d, n, out)
         else:
             with torch.cuda.stream(self.stream):
                 if isinstance(tokens, np.ndarray):

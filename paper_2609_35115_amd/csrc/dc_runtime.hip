@@ -27,6 +27,7 @@
 #include <vector>
 
 #include "../../include/dc.h"
+#include "dc_copy.h"
 #include "dc_internal.h"
 
 using namespace dc;
@@ -105,6 +106,11 @@ struct dc_state {
     hipStream_t side = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
     int src_join = -1;          // index of the launch that reads the source ring
+    // dc_decode_chunk_on: the stream and the end of its last call, whether the
+    // state's own stream has yet to wait for it, and whether it has had work since
+    hipStream_t on_stream = nullptr;
+    hipEvent_t on_ev = nullptr, home_ev = nullptr;
+    bool on_any = false, on_pending = false, home_work = false;
     char* arena = nullptr;
     size_t arena_bytes = 0;
     std::vector<Ring> rings;
@@ -941,19 +947,30 @@ static hipError_t enqueue_step(dc_state* s, int n, hipStream_t st, double* ptab 
     return e;
 }
 
+// The state's own stream, for work: after the calls made on others.
+static hipStream_t home(dc_state* s)
+{
+    s->home_work = true;
+    if (s->on_pending) {
+        s->on_pending = false;
+        if (hipStreamWaitEvent(s->stream, s->on_ev, 0) != hipSuccess) (void)hipEventSynchronize(s->on_ev);
+    }
+    return s->stream;
+}
+
 static hipError_t zero_state(dc_state* s)
 {
-    hipError_t e = hipMemsetAsync(s->arena + s->ring_begin, 0, s->ring_end - s->ring_begin, s->stream);
+    hipError_t e = hipMemsetAsync(s->arena + s->ring_begin, 0, s->ring_end - s->ring_begin, home(s));
     if (e != hipSuccess) return e;
-    e = hipMemsetAsync(s->clock, 0, sizeof(int64_t), s->stream);
+    e = hipMemsetAsync(s->clock, 0, sizeof(int64_t), home(s));
     if (e != hipSuccess) return e;
-    e = hipMemsetAsync(s->start, 0, (size_t)s->cfg.batch * sizeof(int64_t), s->stream);
+    e = hipMemsetAsync(s->start, 0, (size_t)s->cfg.batch * sizeof(int64_t), home(s));
     if (e != hipSuccess) return e;
-    e = launch_init_keys(s->keys, s->cfg.batch, s->stream);
+    e = launch_init_keys(s->keys, s->cfg.batch, home(s));
     if (e != hipSuccess) return e;
-    e = hipMemsetAsync(s->arrivals, 0, sizeof(unsigned), s->stream);
+    e = hipMemsetAsync(s->arrivals, 0, sizeof(unsigned), home(s));
     if (e != hipSuccess) return e;
-    return hipMemsetAsync(s->err, 0, sizeof(int), s->stream);
+    return hipMemsetAsync(s->err, 0, sizeof(int), home(s));
 }
 
 // ------------------------------------------------------------------ the ABI
@@ -1206,12 +1223,41 @@ dc_status dc_init(const void* weights_blob, size_t blob_bytes, const dc_cfg* cfg
     return DC_OK;
 }
 
+// A call on another stream than the state's comes after the last such call
+// and after the state's own stream where that has had work since.  The state's
+// own stream waits for it when it is next used (settle): handing every call
+// over to it and back cost 45 us between the two waits, and a wait on it alone
+// after every call still 26 us, for a tiny decoder's 89 us.
+static hipError_t enter_on(dc_state* s, hipStream_t st)
+{
+    hipError_t e = hipSuccess;
+    if (!s->on_ev) {
+        e = hipEventCreateWithFlags(&s->on_ev, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&s->home_ev, hipEventDisableTiming);
+        s->home_work = true;
+    }
+    if (e == hipSuccess && s->home_work) {
+        e = hipEventRecord(s->home_ev, s->stream);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, s->home_ev, 0);
+    }
+    if (e == hipSuccess && s->on_any && s->on_stream != st) e = hipStreamWaitEvent(st, s->on_ev, 0);
+    return e;
+}
+
+static hipError_t leave_on(dc_state* s, hipStream_t st)
+{
+    s->on_stream = st;
+    s->on_any = s->on_pending = true;
+    s->home_work = false;
+    return hipEventRecord(s->on_ev, st);
+}
+
 // One call: admission, staging of tokens (and f0), replay or direct launch,
 // staging of the PCM.  f0 is non-null exactly for a decoder with a source.
 // static_ptab non-null: dc_decode_chunk_f0_static (direct launches whose phase
 // table is the device's static scratch; never a graph replay).
 static dc_status decode_call(dc_state* s, const int32_t* tokens, const float* f0, int32_t n, float* audio_out,
-                             double* static_ptab = nullptr)
+                             hipStream_t st, double* static_ptab = nullptr)
 {
     if (s->poisoned) return fail(s, DC_ESTATE, "state is poisoned; call dc_reset");
     const dc_cfg& c = s->cfg;
@@ -1239,32 +1285,33 @@ static dc_status decode_call(dc_state* s, const int32_t* tokens, const float* f0
     }
     hipError_t e = hipSuccess;
     if (tokens != s->tok) {
-        e = hipMemcpyAsync(s->tok, tokens, tok_bytes, host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
-                           s->stream);
+        e = host ? hipMemcpyAsync(s->tok, tokens, tok_bytes, hipMemcpyHostToDevice, st)
+                 : stage_async(s->tok, tokens, tok_bytes, s->device, st);
         if (e != hipSuccess) return device_fail(s, e, "token staging");
         s->st.staged_tokens++;
     }
     if (c.n_harmonics > 0 && f0 != s->f0) {
         const size_t f0_bytes = (size_t)c.batch * n * s->fpt[0] * sizeof(float);
-        e = hipMemcpyAsync(s->f0, f0, f0_bytes, host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, s->stream);
+        e = host ? hipMemcpyAsync(s->f0, f0, f0_bytes, hipMemcpyHostToDevice, st)
+                 : stage_async(s->f0, f0, f0_bytes, s->device, st);
         if (e != hipSuccess) return device_fail(s, e, "f0 staging");
         s->st.staged_f0++;
     }
     if (static_ptab) {
-        e = enqueue_step(s, n, s->stream, static_ptab);
+        e = enqueue_step(s, n, st, static_ptab);
         if (e != hipSuccess) return device_fail(s, e, "direct launch (static scratch)");
         s->st.direct_static++;
     } else if (n == c.chunk_tokens && s->exec) {
-        e = hipGraphLaunch(s->exec, s->stream);
+        e = hipGraphLaunch(s->exec, st);
         if (e != hipSuccess) return device_fail(s, e, "hipGraphLaunch");
         s->st.replays++;
     } else if (n < c.chunk_tokens && (size_t)n < s->flush_exec.size() && s->flush_exec[n]) {
-        e = hipGraphLaunch(s->flush_exec[n], s->stream);
+        e = hipGraphLaunch(s->flush_exec[n], st);
         if (e != hipSuccess) return device_fail(s, e, "hipGraphLaunch");
         s->st.replays++;
         s->st.replays_flush++;
     } else {
-        e = enqueue_step(s, n, s->stream);
+        e = enqueue_step(s, n, st);
         if (e != hipSuccess) return device_fail(s, e, "direct launch");
         if (n != c.chunk_tokens) s->st.direct_shape++;
         else s->st.direct_nograph++;
@@ -1272,8 +1319,8 @@ static dc_status decode_call(dc_state* s, const int32_t* tokens, const float* f0
     s->st.calls++;
     s->clock_host += n;
     if (audio_out != s->audio) {
-        e = hipMemcpyAsync(audio_out, s->audio, pcm_bytes, host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice,
-                           s->stream);
+        e = host ? hipMemcpyAsync(audio_out, s->audio, pcm_bytes, hipMemcpyDeviceToHost, st)
+                 : stage_async(audio_out, s->audio, pcm_bytes, s->device, st);
         if (e != hipSuccess) return device_fail(s, e, "audio staging");
         s->st.staged_audio++;
     }
@@ -1288,7 +1335,7 @@ dc_status dc_decode_chunk(dc_state* s, const int32_t* tokens, int32_t n, float* 
         s->st.rejected++;
         return fail(s, DC_EINVAL, "this decoder has a harmonic source: call dc_decode_chunk_f0");
     }
-    return decode_call(s, tokens, nullptr, n, audio_out);
+    return decode_call(s, tokens, nullptr, n, audio_out, home(s));
 }
 
 dc_status dc_decode_chunk_f0(dc_state* s, const int32_t* tokens, const float* f0, int32_t n, float* audio_out)
@@ -1298,7 +1345,29 @@ dc_status dc_decode_chunk_f0(dc_state* s, const int32_t* tokens, const float* f0
         s->st.rejected++;
         return fail(s, DC_EINVAL, "this decoder has no harmonic source: call dc_decode_chunk");
     }
-    return decode_call(s, tokens, f0, n, audio_out);
+    return decode_call(s, tokens, f0, n, audio_out, home(s));
+}
+
+dc_status dc_decode_chunk_on(dc_state* s, void* hip_stream, const int32_t* tokens, const float* f0, int32_t n,
+                             float* audio_out)
+{
+    if (!s) return DC_EINVAL;
+    const char* why = (s->cfg.flags & DC_HOST_PTRS)      ? "a DC_HOST_PTRS state's calls are synchronous"
+                      : (s->cfg.n_harmonics > 0 && !f0)  ? "this decoder has a harmonic source: f0 is needed"
+                      : (s->cfg.n_harmonics == 0 && f0)  ? "this decoder has no harmonic source"
+                                                         : nullptr;
+    if (why) {
+        s->st.rejected++;
+        return fail(s, DC_EINVAL, why);
+    }
+    const hipStream_t st = (hipStream_t)hip_stream;
+    if (st == s->stream) return decode_call(s, tokens, f0, n, audio_out, home(s));
+    hipError_t e = enter_on(s, st);
+    if (e != hipSuccess) return device_fail(s, e, "stream hand-over");
+    const dc_status status = decode_call(s, tokens, f0, n, audio_out, st);
+    e = leave_on(s, st);   // also after a failure: what was launched comes before the state's later work
+    if (e != hipSuccess) return device_fail(s, e, "stream hand-over");
+    return status;
 }
 
 // ------------------------------------------- the static-scratch entry point
@@ -1355,14 +1424,22 @@ dc_status dc_decode_chunk_f0_static(dc_state* s, const int32_t* tokens, const fl
         }
     }
     if (!s->static_ptab) return fail(s, DC_EDEVICE, "static scratch address was not resolved at dc_init");
-    return decode_call(s, tokens, f0, n, audio_out, s->static_ptab);
+    return decode_call(s, tokens, f0, n, audio_out, home(s), s->static_ptab);
+}
+
+dc_status dc_settle(dc_state* s)
+{
+    if (!s) return DC_EINVAL;
+    (void)home(s);
+    return DC_OK;
 }
 
 dc_status dc_sync(dc_state* s)
 {
     if (!s) return DC_EINVAL;
-    hipError_t e = hipStreamSynchronize(s->stream);
+    hipError_t e = hipStreamSynchronize(home(s));
     if (e != hipSuccess) return device_fail(s, e, "hipStreamSynchronize");
+    s->home_work = false;
     int flag = 0;
     e = hipMemcpy(&flag, s->err, sizeof(int), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return device_fail(s, e, "error flag read");
@@ -1379,7 +1456,7 @@ dc_status dc_reset(dc_state* s)
 {
     if (!s) return DC_EINVAL;
     hipError_t e = zero_state(s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(home(s));
     if (e != hipSuccess) return device_fail(s, e, "dc_reset");
     s->poisoned = false;
     s->clock_host = 0;
@@ -1393,11 +1470,11 @@ dc_status dc_reset_stream(dc_state* s, int32_t b)
     for (const Ring& r : s->rings) {
         const size_t es = elem_bytes(r.elem);
         const size_t per = (size_t)r.R * r.C * es;
-        hipError_t e = hipMemsetAsync((char*)r.ptr + (size_t)b * per, 0, per, s->stream);
+        hipError_t e = hipMemsetAsync((char*)r.ptr + (size_t)b * per, 0, per, home(s));
         if (e != hipSuccess) return device_fail(s, e, "dc_reset_stream");
     }
     // fused pairs recompute h of the left context: frames before this point are zeros
-    hipError_t e = launch_mark_start(s->start, s->keys, b, s->clock, 0, (uint64_t)b, s->stream);
+    hipError_t e = launch_mark_start(s->start, s->keys, b, s->clock, 0, (uint64_t)b, home(s));
     if (e != hipSuccess) return device_fail(s, e, "dc_reset_stream");
     return DC_OK;
 }
@@ -1494,7 +1571,7 @@ dc_status dc_carry_export(dc_state* s, int32_t b, void* host_out, size_t bytes)
     if (b < 0 || b >= s->cfg.batch || !host_out) return fail(s, DC_EINVAL, "bad stream index or buffer");
     if (bytes != snapshot_bytes(s)) return fail(s, DC_EINVAL, "buffer size differs from dc_carry_bytes");
     if (s->poisoned) return fail(s, DC_ESTATE, "state is poisoned; call dc_reset");
-    hipError_t e = hipStreamSynchronize(s->stream);
+    hipError_t e = hipStreamSynchronize(home(s));
     if (e != hipSuccess) return device_fail(s, e, "dc_carry_export");
     int64_t start = 0;
     uint64_t key = 0;
@@ -1540,7 +1617,7 @@ dc_status dc_carry_import(dc_state* s, int32_t b, const void* host_in, size_t by
         return fail(s, DC_EINVAL, "snapshot of a different architecture, dtype or ring layout");
     if (hd.position < 0) return fail(s, DC_EINVAL, "bad snapshot position");
     if (s->poisoned) return fail(s, DC_ESTATE, "state is poisoned; call dc_reset");
-    hipError_t e = hipStreamSynchronize(s->stream);
+    hipError_t e = hipStreamSynchronize(home(s));
     if (e != hipSuccess) return device_fail(s, e, "dc_carry_import");
     // the stream's rings start clean, then take the carried frames
     for (const Ring& r : s->rings) {
@@ -1567,8 +1644,8 @@ dc_status dc_carry_import(dc_state* s, int32_t b, const void* host_in, size_t by
         if (e != hipSuccess) return device_fail(s, e, "dc_carry_import");
     }
     // the stream started `position` tokens before this state's next call
-    e = launch_mark_start(s->start, s->keys, b, s->clock, hd.position, hd.key, s->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+    e = launch_mark_start(s->start, s->keys, b, s->clock, hd.position, hd.key, home(s));
+    if (e == hipSuccess) e = hipStreamSynchronize(home(s));
     if (e != hipSuccess) return device_fail(s, e, "dc_carry_import");
     return DC_OK;
 }
@@ -1599,7 +1676,7 @@ dc_status dc_tap_read(dc_state* s, int32_t tap, int32_t b, int64_t frame0, int32
     if (channels) *channels = r.C;
     const int64_t end = s->clock_host * s->fpt[r.level];
     if (frame0 < end - r.R || frame0 + nframes > end) return fail(s, DC_ERANGE, "frames not held by the ring");
-    hipError_t e = hipStreamSynchronize(s->stream);
+    hipError_t e = hipStreamSynchronize(home(s));
     if (e != hipSuccess) return device_fail(s, e, "dc_tap_read");
     const size_t es = elem_bytes(r.elem);
     std::vector<char> row((size_t)r.C * es);
@@ -1717,11 +1794,11 @@ dc_status dc_time_layers(dc_state* s, int32_t reps, double* us_per_launch)
     if (e == hipSuccess) e = hipEventCreate(&e1);
     const int nl = layer_count(s);
     for (int i = 0; i < nl && e == hipSuccess; i++) {   // re-runs leave the clock where it is
-        e = launch_layer(s, i, s->cfg.chunk_tokens, s->stream, nullptr, true);   // warm
-        if (e == hipSuccess) e = hipEventRecord(e0, s->stream);
+        e = launch_layer(s, i, s->cfg.chunk_tokens, home(s), nullptr, true);   // warm
+        if (e == hipSuccess) e = hipEventRecord(e0, home(s));
         for (int r = 0; r < reps && e == hipSuccess; r++)
-            e = launch_layer(s, i, s->cfg.chunk_tokens, s->stream, nullptr, true);
-        if (e == hipSuccess) e = hipEventRecord(e1, s->stream);
+            e = launch_layer(s, i, s->cfg.chunk_tokens, home(s), nullptr, true);
+        if (e == hipSuccess) e = hipEventRecord(e1, home(s));
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
@@ -1738,6 +1815,7 @@ const char* dc_last_error(const dc_state* s) { return s ? s->msg.c_str() : g_ini
 void dc_free(dc_state* s)
 {
     if (!s) return;
+    if (s->on_pending) (void)hipEventSynchronize(s->on_ev);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     if (s->exec) (void)hipGraphExecDestroy(s->exec);
     if (s->graph) (void)hipGraphDestroy(s->graph);
@@ -1747,6 +1825,8 @@ void dc_free(dc_state* s)
         if (g) (void)hipGraphDestroy(g);
     if (s->side) (void)hipStreamSynchronize(s->side);
     if (s->arena) (void)hipFree(s->arena);
+    if (s->on_ev) (void)hipEventDestroy(s->on_ev);
+    if (s->home_ev) (void)hipEventDestroy(s->home_ev);
     if (s->fork_ev) (void)hipEventDestroy(s->fork_ev);
     if (s->join_ev) (void)hipEventDestroy(s->join_ev);
     if (s->side) (void)hipStreamDestroy(s->side);
