@@ -74,6 +74,15 @@ __device__ __forceinline__ float row_sum(float v)
     return v;
 }
 
+// v plus the value of the lane 16 apart (within pairs of DPP rows).
+__device__ __forceinline__ float sum_xor16(float v)
+{
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const uint32_t a0 = a[0], a1 = a[1];   // (scalars: a bit cast straight from element 1 reads element 0)
+    return __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1);
+}
+
 // Frame where the call's own frames start in stream b's carry regions.
 __device__ __forceinline__ int own_base(const CarryRef& c, int prompt, int b)
 {
@@ -145,46 +154,6 @@ __device__ __forceinline__ void epilogue4(const GemmParams& p, int row, int col,
             }
         }
     }
-}
-
-// LayerNorm statistics of rows m0 .. m0 + 255 / TPR of h [M][K] (K <= 512):
-// TPR adjacent threads share a row, thread t taking row t / TPR and columns
-// [(t % TPR) K / TPR, (t % TPR + 1) K / TPR).  Returns the row's mean and
-// 1 / sqrt(var + eps); the thread's values stay in v.  Mean and variance come
-// from sums shifted by the row's first value.
-struct LnRow {
-    float mean, rstd;
-};
-template <int TPR, int NV>
-__device__ __forceinline__ LnRow ln_row_stats(const float* h, int M, int K, int m0, f32x4 (&v)[NV])
-{
-    const int tid = threadIdx.x, lane = tid & 63, q = tid % TPR;
-    const int row = min(m0 + tid / TPR, M - 1);
-    const int kq = K / TPR, nv = kq >> 2;
-    const f32x4* hr = (const f32x4*)(h + (size_t)row * K + q * kq);
-    // every load is issued (clamped into the thread's columns) before any is used
-#pragma unroll
-    for (int i = 0; i < NV; i++) v[i] = hr[min(i, nv - 1)];
-    const float x0 = __shfl(v[0][0], lane & ~(TPR - 1), 64);
-    float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-    for (int i = 0; i < NV; i++) {
-        const float live = i < nv ? 1.0f : 0.0f;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const float d = (v[i][e] - x0) * live;
-            s1 += d;
-            s2 += d * d;
-        }
-    }
-#pragma unroll
-    for (int o = 1; o < TPR; o <<= 1) {
-        s1 += __shfl_xor(s1, o, 64);
-        s2 += __shfl_xor(s2, o, 64);
-    }
-    const float md = s1 / (float)K;
-    const float var = fmaxf(s2 / (float)K - md * md, 0.f);
-    return LnRow{x0 + md, 1.0f / sqrtf(var + 1e-6f)};
 }
 
 // GEMM of many rows (calls of more than kSkinnyRows).  A block computes 16 MB
@@ -672,24 +641,61 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmParams p)
     }
 
     if constexpr (LN) {
-        float* ss = (float*)(smem + (size_t)16 * RB * LDA * sizeof(T));
+        // TPR threads per row, thread q taking the row's 4-column vectors
+        // q, q + TPR, ... (whole lines of a row per load), their sums added
+        // across DPP rows; each thread a contiguous run, added by shuffles, took
+        // 9.0 and 8.8 us per QKV and MLP-up launch at 112 rows in bf16, now 8.2
+        // and 8.1 (fp32 11.5 and 12.0, now 10.5 and 11.0).  Scale and shift go
+        // through LDS: in registers they cost a block per CU.  Mean and variance
+        // come from sums shifted by the row's first value.
+        float* ss = (float*)(smem + (size_t)16 * RB * LDA * sizeof(T));   // 1 + scale, shift
+        static_assert(TPR == 16 || TPR == 32, "one or two DPP rows per LayerNorm row");
+        constexpr int NV = 128 / TPR;                 // K <= 512
+        const int r = tid / TPR, q = tid % TPR, nv = p.K / (4 * TPR);
+        const f32x4* hr = (const f32x4*)(p.ln_h + (size_t)min(m0 + r, p.M - 1) * p.K) + q;
+        f32x4 v[NV];
+#pragma unroll
+        for (int i = 0; i < NV; i++) v[i] = hr[TPR * min(i, nv - 1)];
         for (int k4 = tid; k4 < (p.K >> 2); k4 += 64 * NW) {
-            ((f32x4*)ss)[k4] = ((const f32x4*)p.ln_scale)[k4];
+            const f32x4 sc = ((const f32x4*)p.ln_scale)[k4];
+            ((f32x4*)ss)[k4] = f32x4{1.0f + sc[0], 1.0f + sc[1], 1.0f + sc[2], 1.0f + sc[3]};
             ((f32x4*)(ss + p.K))[k4] = ((const f32x4*)p.ln_shift)[k4];
         }
-        // TPR threads per row, K / TPR columns each
-        f32x4 v[128 / TPR];
-        const LnRow st = ln_row_stats<TPR, 128 / TPR>(p.ln_h, p.M, p.K, m0, v);
-        __syncthreads();
-        const int r = tid / TPR, kq = p.K / TPR, nv = kq >> 2, kb = (tid % TPR) * kq;
+        float x0, s1 = 0.f, s2 = 0.f;
+        if constexpr (TPR == 16) {
+            x0 = row_ror<0x150>(v[0][0]);             // lane 0 of the DPP row
+        } else {
+            const int u = __builtin_bit_cast(int, v[0][0]);
+            const int lo = __builtin_amdgcn_readlane(u, 0), hi = __builtin_amdgcn_readlane(u, 32);
+            x0 = __builtin_bit_cast(float, lane < 32 ? lo : hi);
+        }
 #pragma unroll
-        for (int i = 0; i < 128 / TPR; i++)
+        for (int i = 0; i < NV; i++)
             if (i < nv) {
-                const int k = kb + 4 * i;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const float d = v[i][e] - x0;
+                    s1 += d;
+                    s2 = fmaf(d, d, s2);
+                }
+            }
+        s1 = row_sum(s1);
+        s2 = row_sum(s2);
+        if constexpr (TPR == 32) {
+            s1 = sum_xor16(s1);
+            s2 = sum_xor16(s2);
+        }
+        const float md = s1 / (float)p.K;
+        const float mean = x0 + md, rstd = 1.0f / sqrtf(fmaxf(s2 / (float)p.K - md * md, 0.f) + 1e-6f);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NV; i++)
+            if (i < nv) {
+                const int k = 4 * (q + TPR * i);
                 const f32x4 sc = *(const f32x4*)(ss + k), sh = *(const f32x4*)(ss + p.K + k);
                 f32x4 a;
 #pragma unroll
-                for (int u = 0; u < 4; u++) a[u] = (v[i][u] - st.mean) * st.rstd * (1.0f + sc[u]) + sh[u];
+                for (int e = 0; e < 4; e++) a[e] = fmaf((v[i][e] - mean) * rstd, sc[e], sh[e]);
                 store4<BF16>(As, (size_t)r * LDA + k, a);
             }
         __syncthreads();

@@ -318,6 +318,28 @@ def test_tiled_gemm_edges_match_oracle(dtype, dim, mlp, f_call, B):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dim,f_call,B", [
+    (128, 1, 1),     # two rows, one 4-column vector a thread, 32 threads a row
+    (192, 13, 3),    # 16 threads a row, three vectors each; a ragged last row tile
+    (384, 11, 2),    # 32 threads a row, three vectors each
+    (512, 15, 17),   # four vectors each; 510 rows, the most but two
+])
+def test_skinny_layernorm_edges_match_oracle(dtype, dim, f_call, B):
+    """Calls of at most 512 rows: the skinny GEMM's LayerNorm at its row splits."""
+    a = dict(TINY, dim=dim, heads=dim // 64, mlp=2 * dim, n_mel=24, depth=1, n_steps=2, f_prompt=9, f_retained=4,
+             f_chunk=1, f_call=f_call)
+    blob = synth.make_flow_weights(a, 12)
+    calls = [f_call, f_call]
+    dec, outs, mu, prompts = _run_gpu(a, dtype, blob, B, a["f_prompt"], calls)
+    for b in {0, B - 1}:
+        _s, ref = _run_oracle(a, dtype, blob, b, prompts[b], mu[b], calls)
+        for k, (g, r) in enumerate(zip(outs, ref)):
+            e, _ = err_stats(g[b], r)
+            assert e <= TOL[dtype], f"stream {b} call {k}: {e:.3e}"
+    dec.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("f_prompt,f_chunk,f_call", [
     (1, 1, 1),       # one key in a prompt, then two tiles of one key: half of the waves have none
     (31, 8, 13),     # tiles cut short by one key, by many
