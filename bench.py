@@ -45,7 +45,8 @@ PROFILES = os.path.join(ROOT, "profiles")
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 DEFAULT_WORKLOAD = "real_f32_b1_n25"
 RNG_SEED = 11   # key of the harmonic source's generator (workloads with a source)
-PEAK = {"hbm": 8000.0, "bf16": 2500.0, "f32": 157.3}   # GB/s, TFLOP/s (MI355X, dense)
+# GB/s, TFLOP/s (MI355X, dense); f32x3: fp32 products as six bf16 ones of three planes
+PEAK = {"hbm": 8000.0, "bf16": 2500.0, "f32": 157.3, "f32x3": 2500.0 / 6}
 
 
 class _Addr:
@@ -141,8 +142,9 @@ def roofline(layers, us, dtype):
         g["launches"] += 1
     name, g = max(groups.items(), key=lambda kv: kv[1]["us"])
     step_us = sum(us)
-    conv = name.startswith(("dc::conv_kernel", "dc::wconv_kernel", "dc::pair_kernel"))   # MFMA kernels
-    op = "bf16" if "<true" in name or name.startswith(("dc::pair_kernel", "dc::wconv_kernel")) else "f32"
+    conv = name.startswith(("dc::conv_kernel", "dc::xconv_kernel", "dc::wconv_kernel", "dc::pair_kernel"))   # MFMA
+    op = "f32x3" if name.startswith("dc::xconv_kernel") else \
+        "bf16" if "<true" in name or name.startswith(("dc::pair_kernel", "dc::wconv_kernel")) else "f32"
     if conv and g["flops"] / g["bytes"] > PEAK[op] * 1e12 / (PEAK["hbm"] * 1e9):
         bound, achieved, peak, unit = "mfma", g["flops"] / (g["us"] * 1e-6) / 1e12, PEAK[op], "TFLOP/s"
     else:

@@ -18,6 +18,10 @@ enum Elem : int { kF32 = 0, kBF16 = 1, kF16 = 2 };
 // to infinity, or NaN) was about to be stored in a bf16 state's residual stream.
 enum ErrBit : int { kErrTokenId = 1, kErrF16Range = 2 };
 
+// How a conv's operands reach the matrix cores: fp32 MFMA, bf16 MFMA, or fp32
+// values as three bf16 planes on the bf16 MFMA.
+enum OpKind : int { kOpF32 = 0, kOpBF16 = 1, kOpX3 = 2 };
+
 inline int elem_bytes(int e) { return e == kF32 ? 4 : 2; }
 
 // A ring of frames for B streams: frame with absolute index tau of stream b
@@ -179,13 +183,16 @@ hipError_t launch_pair(int v, const PairParams* ps, int count, hipStream_t st);
 
 // The tile shapes compiled for each operand type.
 int num_tile_variants();
+constexpr int kForcedTiles = 29;   // the shapes a caller may ask for; the rest are three planes' own
 TileShape tile_variant(int v);
 
-// LDS bytes a conv launch needs with tile shape v.
-size_t conv_lds_bytes(int v, bool bf16, const ConvParams& p);
+// Whether shape v is compiled for operand kind op (an OpKind), and the LDS
+// bytes a conv launch needs with it.
+bool tile_exists(int v, int op);
+size_t conv_lds_bytes(int v, int op, const ConvParams& p);
 
 // LDS bytes of a launch of `count` convs (the largest member).
-hipError_t launch_conv(int v, bool bf16, const ConvParams* ps, int count, hipStream_t st);
+hipError_t launch_conv(int v, int op, const ConvParams* ps, int count, hipStream_t st);
 
 hipError_t launch_embed(const int32_t* tokens, int n, int B, const void* table, int vocab, int C,
                         int elem, int fpt, Ring out, const int64_t* clock, int* err, hipStream_t st);

@@ -166,24 +166,45 @@ __device__ __forceinline__ size_t ring_at(int b, int B, int64_t slot, int64_t R,
 
 // ----------------------------------------------------- operand type traits
 
-template <bool BF16> struct OpT;
+// Operand kinds (an OpKind): fp32, bf16, and fp32 as three bf16 planes.
+template <int OP> struct OpT;
 
 // bf16 operands: v_mfma_f32_16x16x32_bf16, lane l holds 8 consecutive K
 // values (channels 8*(l/16) .. +7 of a 32-channel chunk) of row/col l%16.
-template <> struct OpT<true> {
+template <> struct OpT<kOpBF16> {
     using T = uint16_t;
     static constexpr int KQ = 32;   // channels per MFMA step
     static constexpr int PAD = 8;   // LDS row padding (elements)
+    static constexpr int PL = 1;    // planes of a value
 };
 
 // fp32 operands: v_mfma_f32_16x16x4_f32 four times per 16-channel chunk; in
 // step q lane l holds channel 4*(l/16) + q, so one 16-byte load per lane
 // feeds four steps.
-template <> struct OpT<false> {
+template <> struct OpT<kOpF32> {
     using T = float;
     static constexpr int KQ = 16;
     static constexpr int PAD = 4;
+    static constexpr int PL = 1;
 };
+
+// fp32 operands on the bf16 MFMA: every value as the exact sum of three
+// bfloat16 (hi, mid, lo: 8 significant bits each, every residual rounded to
+// nearest), and a product as the six bf16 products of a weight of at least
+// 2^-18 of it, the leading one in an fp32 accumulator of its own, which so is
+// rounded once per 32 channels, the five small ones in another.  What is left
+// out is below 2^-25 of a product, less than its rounding in fp32, and the
+// whole decode is nearer to 64 bits than with fp32 MFMAs (real decoder: 5.2e-7
+// against 7.8e-7).  Six bf16 MFMAs take 6/16 of the time of the fp32 MFMAs for
+// the same products; a value's fragments are 6 bytes instead of 4.
+template <> struct OpT<kOpX3> {
+    using T = uint16_t;
+    static constexpr int KQ = 32;
+    static constexpr int PAD = 8;
+    static constexpr int PL = 3;
+};
+constexpr int kX3 = 6;   // the (weight, frame) planes of an MFMA step's products, in order
+constexpr int kX3W[kX3] = {0, 0, 1, 1, 0, 2}, kX3A[kX3] = {0, 1, 0, 1, 2, 0};
 
 // Load 8 channels of one frame as floats.
 __device__ __forceinline__ void load8(const void* base, int elem, size_t off, float v[8])
@@ -236,6 +257,41 @@ __device__ __forceinline__ void store8_lds(float* dst, const float v[8])
     f32x4 a = {v[0], v[1], v[2], v[3]}, b = {v[4], v[5], v[6], v[7]};
     *(f32x4*)dst = a;
     *(f32x4*)(dst + 4) = b;
+}
+
+// v = hi + mid + lo exactly, planes `stride` elements apart.  A magnitude that
+// rounds past bfloat16 is cut instead, and an infinity or NaN is its own hi
+// with nothing after it.
+__device__ __forceinline__ void store8_lds_x3(uint16_t* dst, int stride, const float v[8])
+{
+    u32x4 h, m, l;
+    float big = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        const float a = v[2 * e], b = v[2 * e + 1];
+        big = fmaxf(big, fmaxf(fabsf(a), fabsf(b)));
+        h[e] = pack_bf16x2(a, b);
+        const float ra = a - bf2f(h[e] & 0xffffu), rb = b - __uint_as_float(h[e] & 0xffff0000u);
+        m[e] = pack_bf16x2(ra, rb);
+        l[e] = pack_bf16x2(ra - bf2f(m[e] & 0xffffu), rb - __uint_as_float(m[e] & 0xffff0000u));
+    }
+    if (big >= 3.3895e38f) {   // (the largest bfloat16 is 3.38953e38)
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const uint32_t u = __float_as_uint(v[e]);
+            const bool fin = (u & 0x7f800000u) != 0x7f800000u;
+            const uint32_t hh = fin ? u >> 16 : f2bf(v[e]);
+            const float r = fin ? v[e] - __uint_as_float(u & 0xffff0000u) : 0.f;
+            const uint32_t mm = f2bf(r), ll = f2bf(r - bf2f(mm));
+            const int sh = 16 * (e & 1);
+            h[e >> 1] = (h[e >> 1] & (0xffff0000u >> sh)) | (hh << sh);
+            m[e >> 1] = (m[e >> 1] & (0xffff0000u >> sh)) | (mm << sh);
+            l[e >> 1] = (l[e >> 1] & (0xffff0000u >> sh)) | (ll << sh);
+        }
+    }
+    *(u32x4*)dst = h;
+    *(u32x4*)(dst + stride) = m;
+    *(u32x4*)(dst + 2 * stride) = l;
 }
 
 // ------------------------------------------------------------ causal conv
@@ -341,12 +397,13 @@ __device__ __forceinline__ void store_out4(const ConvParams& p, int b, const Out
 // Operand rows [t0 - halo, t0 - halo + rows) of channel block cb of stream b,
 // read through the input ring (ring slot base_in holds row 0), LeakyReLU'd
 // if asked, converted once to the operand type (bf16: optionally as hi + lo
-// halves, the lo rows lo_off elements after the hi rows) and stored in LDS
+// halves; three planes: always; the next plane's rows lo_off elements after
+// the one before) and stored in LDS
 // rows of LDW elements.  Rows at or past the call's frames are zeros.
-template <bool BF16, int CB, int LDW>
+template <int OP, int CB, int LDW>
 __device__ __forceinline__ void stage_operand(const ConvParams& p, const void* in_ptr, int in_R, int b, int t0,
                                               int halo, int rows, int base_in, int cb,
-                                              typename OpT<BF16>::T* lds, int lo_off)
+                                              typename OpT<OP>::T* lds, int lo_off)
 {
     constexpr int VPR = CB / 8;
     for (int v = threadIdx.x; v < rows * VPR; v += 256) {
@@ -361,7 +418,9 @@ __device__ __forceinline__ void stage_operand(const ConvParams& p, const void* i
                 for (int e = 0; e < 8; e++) x[e] = lrelu(x[e], p.slope);
             }
         }
-        if constexpr (BF16) {
+        if constexpr (OP == kOpX3) {
+            store8_lds_x3(lds + r * LDW + c8, lo_off, x);
+        } else if constexpr (OP == kOpBF16) {
             if (p.split)
                 store8_lds_split(lds + r * LDW + c8, lds + lo_off + r * LDW + c8, x);
             else
@@ -476,9 +535,10 @@ __device__ __forceinline__ void store_tile(const ConvParams& p, const OutRef& rs
         store_tile_e<MB, NB, kBF16>(p, rs, acc, bias, b, t0, n0, row0, colblk0, lane);
 }
 
-template <bool BF16, int MB, int NB, int WGM, int WGN, int WGK, int KCH>
-__global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
+template <int OP, int MB, int NB, int WGM, int WGN, int WGK, int KCH>
+__device__ __forceinline__ void conv_body(const ConvGroup& g)
 {
+    constexpr bool BF16 = OP == kOpBF16, X3 = OP == kOpX3;
     // shared fields from member 0; this block's member supplies the rest
     const ConvParams& p = g.p;
     const void* in_ptr = p.in;
@@ -499,9 +559,10 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
         rs.res_R = (int)m.res_R;
         k = m.k;
     }
-    using Tr = OpT<BF16>;
+    using Tr = OpT<OP>;
     using T = typename Tr::T;
-    using Frag = typename std::conditional<BF16, u32x4, f32x4>::type;
+    using Frag = typename std::conditional<OP == kOpF32, f32x4, u32x4>::type;
+    constexpr int PL = Tr::PL;
     constexpr int BM = 16 * MB * WGM, BN = 16 * NB * WGN, S = WGK;
     constexpr int CB = Tr::KQ * KCH;        // channels per block
     constexpr int KPW = KCH / WGK;          // this wave's K chunks per tap
@@ -525,8 +586,8 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
     const int nblk0 = n0 / 16 + wn * NB;
     const Frag* wp = reinterpret_cast<const Frag*>(w_ptr);
 
-    // K-split tiles hold at most one output vector per thread in the
-    // epilogue: its bias and residual are loaded here, before the K loop, so
+    // K-split tiles hold one output vector per thread in the epilogue (tiles of
+    // more than 1024 outputs: one per pass of 1024): the first one's bias and residual are loaded here, before the K loop, so
     // the epilogue does not wait for them (a vector with a branch mean, or at
     // the edge of the output, loads what it adds there instead)
     const int e_idx = tid * 4;
@@ -541,7 +602,7 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
     u32x4 e_raw = {0u, 0u, 0u, 0u};
     bool e_pre = false;
     if constexpr (WGK > 1) {
-        static_assert(BM * BN <= 4 * 256, "one output vector per thread");
+        static_assert(BM * BN <= 1024 || BM * BN % 1024 == 0 && 1024 % BN == 0, "whole passes, each thread in its columns");
         if (e_live) {
             const int nv = p.N - e_n4 < 4 ? p.N - e_n4 : 4;
 #pragma unroll
@@ -564,10 +625,14 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
     }
 
     f32x4 acc[MB][NB];
+    f32x4 low[X3 ? MB : 1][X3 ? NB : 1];   // three planes: the products below the leading one
 #pragma unroll
     for (int i = 0; i < MB; i++)
 #pragma unroll
-        for (int j = 0; j < NB; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NB; j++) {
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (X3) low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
 
     // Weight fragments of this wave for tap j of channel block cb.  Column
     // blocks past the layer's last one re-read that block (unconditional
@@ -581,10 +646,10 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
     // fragments one step ahead, each in a ring of three register buffers,
     // so neither the L2 nor the LDS latency sits between two steps' MFMAs.
     // Every accumulator still adds its steps in ascending (tap, chunk) order.
-    using AFrag = typename std::conditional<BF16, u32x4, f32x4>::type;   // frames of one K chunk
-    constexpr int VEC = BF16 ? 8 : 4;       // operand elements per lane per K chunk
+    using AFrag = Frag;   // frames of one K chunk
+    constexpr int VEC = OP == kOpF32 ? 4 : 8;   // operand elements per lane per K chunk
     const T* a_lane = lds + (wm * 16 * MB + (lane & 15)) * LDW + (lane >> 4) * VEC + wk * Tr::KQ;
-    const int lo_off = rows * LDW;          // low halves of a split operand
+    const int lo_off = rows * LDW;          // the next plane (low halves of a split operand)
     const int nsteps = k * KPW;
     auto load_w = [&](int cb, int st, Frag (&w)[NB]) {
         st = st < nsteps ? st : nsteps - 1;
@@ -631,40 +696,60 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
                 for (int mb = 0; mb < MB; mb++)
 #pragma unroll
                     for (int nb = 0; nb < NB; nb++)
-                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][q], a[mb][q], acc[mb][nb], 0, 0, 0);
+                        if constexpr (!X3)
+                            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][q], a[mb][q], acc[mb][nb], 0, 0, 0);
         }
     };
 
     // Operand rows [t0 - halo, t0 + BM) of channel block cb, through the ring.
     auto load_operand = [&](int cb) {
-        stage_operand<BF16, CB, LDW>(p, in_ptr, in_R, b, t0, halo, rows, base_in, cb, lds, lo_off);
+        stage_operand<OP, CB, LDW>(p, in_ptr, in_R, b, t0, halo, rows, base_in, cb, lds, lo_off);
     };
 
     // Large per-wave tiles (at least 8 fragments): the step pipeline below.
     // Small ones: whole taps in pairs (two tap buffers of weights, frames read
     // as needed), where the per-step bookkeeping would outweigh the MFMAs.
+    // (Three planes of a large tile's buffers would not fit the registers.)
     constexpr bool PIPE = MB * NB >= 8;
+    static_assert(!(X3 && PIPE), "no large tiles of three planes");
     if constexpr (!PIPE) {
         // weight fragments of this wave for tap j of channel block cb
-        auto load_tap = [&](int cb, int j, Frag (&w)[KPW][NB]) {
-            const Frag* wt = wp + (size_t)(cb * k + j) * KCH * p.NB16 * 64 + lane;
+        auto load_tap = [&](int cb, int j, Frag (&w)[KPW][NB * PL]) {
+            const Frag* wt = wp + (size_t)(cb * k + j) * KCH * p.NB16 * PL * 64 + lane;
 #pragma unroll
             for (int ki = 0; ki < KPW; ki++)
 #pragma unroll
-                for (int nb = 0; nb < NB; nb++) w[ki][nb] = wt[((size_t)(ki * WGK + wk) * p.NB16 + nblk[nb]) * 64];
+                for (int nb = 0; nb < NB; nb++)
+#pragma unroll
+                    for (int q = 0; q < PL; q++)
+                        w[ki][nb * PL + q] = wt[(((size_t)(ki * WGK + wk) * p.NB16 + nblk[nb]) * PL + q) * 64];
         };
         // MFMAs of tap j: this lane's fragment address is fixed; a tap adds a
         // row offset, a block / chunk an immediate
-        auto compute_tap = [&](int j, const Frag (&w)[KPW][NB]) {
+        auto compute_tap = [&](int j, const Frag (&w)[KPW][NB * PL]) {
             DC_DBG_CHECK(wm * 16 * MB + 16 * MB - 1 + j * p.d < rows, kDbgTile);
             const T* aj = a_lane + j * p.d * LDW;
 #pragma unroll
             for (int ki = 0; ki < KPW; ki++) {
                 const int koff = ki * WGK * Tr::KQ;
-                AFrag a[MB];
+                AFrag a[MB * PL];
 #pragma unroll
-                for (int mb = 0; mb < MB; mb++) a[mb] = *(const AFrag*)(aj + mb * 16 * LDW + koff);
-                if constexpr (BF16) {
+                for (int mb = 0; mb < MB; mb++)
+#pragma unroll
+                    for (int q = 0; q < PL; q++) a[mb * PL + q] = *(const AFrag*)(aj + q * lo_off + mb * 16 * LDW + koff);
+                if constexpr (X3) {
+#pragma unroll
+                    for (int q = 0; q < kX3; q++)
+#pragma unroll
+                        for (int mb = 0; mb < MB; mb++)
+#pragma unroll
+                            for (int nb = 0; nb < NB; nb++) {
+                                f32x4& d = q == 0 ? acc[mb][nb] : low[mb][nb];
+                                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(bf16x8_t, w[ki][nb * PL + kX3W[q]]),
+                                    __builtin_bit_cast(bf16x8_t, a[mb * PL + kX3A[q]]), d, 0, 0, 0);
+                            }
+                } else if constexpr (BF16) {
 #pragma unroll
                     for (int mb = 0; mb < MB; mb++)
 #pragma unroll
@@ -695,7 +780,7 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
                 }
             }
         };
-        Frag w0[KPW][NB], w1[KPW][NB];
+        Frag w0[KPW][NB * PL], w1[KPW][NB * PL];
         for (int cb = 0; cb < p.n_cb; cb++) {
             __syncthreads();
             load_tap(cb, 0, w0);
@@ -749,6 +834,13 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
     }
     }
 
+    if constexpr (X3) {
+#pragma unroll
+        for (int i = 0; i < MB; i++)
+#pragma unroll
+            for (int j = 0; j < NB; j++) acc[i][j] += low[i][j];
+    }
+
     // ---- epilogue: bias, residual, branch mean, LeakyReLU, store through the rings
     const int64_t tau_out0 = (tau0 + t0) * p.u;   // output frame of block row 0, phase 0
     rs.out_s = (int)ring_slot(tau_out0, rs.out_R);
@@ -777,14 +869,16 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
                 *(f32x4*)(red + (wk * BM + row) * BN + col) = acc[mb][nb];
             }
         __syncthreads();
-        if (e_live) {
-            f32x4 v = *(const f32x4*)(red + e_idx);
+        for (int i = 0; i < (BM * BN + 1023) / 1024; i++) {
+            const int idx = e_idx + i * 1024, tl = e_tl + i * (1024 / BN);
+            if (i == 0 ? !e_live : t0 + tl >= p.F || e_n4 >= p.N) continue;
+            f32x4 v = *(const f32x4*)(red + idx);
 #pragma unroll
-            for (int q = 1; q < S; q++) v = v + *(const f32x4*)(red + q * BM * BN + e_idx);
+            for (int q = 1; q < S; q++) v = v + *(const f32x4*)(red + q * BM * BN + idx);
             v = v + e_bias;
             const int rpn = p.u == 1 ? 0 : e_n4 / p.out_C;
-            const int off = e_tl * p.u + rpn, co = e_n4 - rpn * p.out_C;
-            if (e_pre) {   // the vector path of store_out4, with the residual loaded up front
+            const int off = tl * p.u + rpn, co = e_n4 - rpn * p.out_C;
+            if (e_pre && i == 0) {   // the vector path of store_out4, with the residual loaded up front
                 if (p.src) v = v + src_term4(p, b, slot_add(rs.src_s, off, (int)p.src_R), co);
                 if (rs.res) {
                     const f32x4 e_res =
@@ -807,6 +901,34 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup g)
         }
     }
     raise_f16_range(p.err, rs.f16_mag);
+}
+
+// The argument of a kernel that takes one, where it lies: a reference to the
+// parameter itself makes the compiler copy all of it to scratch once a body
+// reads it in more places than it folds (456 bytes a lane, times twice as long).
+template <class A>
+__device__ __forceinline__ const A& kernel_arg()
+{
+    return *(const A*)(const __attribute__((address_space(4))) A*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+template <bool BF16, int MB, int NB, int WGM, int WGN, int WGK, int KCH>
+__global__ __launch_bounds__(256) void conv_kernel(const ConvGroup)
+{
+    conv_body<BF16 ? kOpBF16 : kOpF32, MB, NB, WGM, WGN, WGK, KCH>(kernel_arg<ConvGroup>());
+}
+
+// fp32 as three bf16 planes.  At batch 1 the launches are bound by load latency
+// and, in the 256-channel stage, by reading its weights (6 bytes each, 50 MB
+// over its launches), with more streams by L2's weight stream again: tiles are
+// as large as leaves each SIMD a wave.  Us per launch of the three branches,
+// fp32 MFMA and planes, dilation 1: batch 1, n = 25, 256 channels 18.3 and 17.4,
+// 128 channels 18.5 and 12.6, 64 channels 16.3 and 12.5; batch 5, n = 25, 75.8
+// and 41.3, 78.4 and 47.0, 59.9 and 39.5.
+template <int MB, int NB, int WGM, int WGN, int WGK, int KCH>
+__global__ __launch_bounds__(256) void xconv_kernel(const ConvGroup)
+{
+    conv_body<kOpX3, MB, NB, WGM, WGN, WGK, KCH>(kernel_arg<ConvGroup>());
 }
 
 // ------------------------------------------- conv with an LDS weight ring
@@ -847,7 +969,7 @@ __global__ __launch_bounds__(256, 2) void wconv_kernel(const ConvGroup g)
     }
     using T = uint16_t;
     constexpr int BM = 16 * MB * WGM, BN = 16 * NB * WGN;
-    constexpr int CB = 32 * KCH, LDW = CB + OpT<true>::PAD;
+    constexpr int CB = 32 * KCH, LDW = CB + OpT<kOpBF16>::PAD;
     constexpr int NFR = BN / 16;            // weight fragments (16 columns x 32 channels) per K step
     constexpr int FPW = NFR / 4;            // of which each wave loads FPW
     static_assert(WGM * WGN == 4 && NFR % 4 == 0, "wide tile shape");
@@ -945,7 +1067,7 @@ __global__ __launch_bounds__(256, 2) void wconv_kernel(const ConvGroup g)
     for (int cb = 0; cb < p.n_cb; cb++) {
         const int s0 = cb * kk;
         if (cb > 0) __syncthreads();   // every wave is done with the previous channel block's rows
-        stage_operand<true, CB, LDW>(p, in_ptr, in_R, b, t0, halo, rows, base_in, cb, lds, lo_off);
+        stage_operand<kOpBF16, CB, LDW>(p, in_ptr, in_R, b, t0, halo, rows, base_in, cb, lds, lo_off);
         // the rows (and, since their loads wait for every earlier load, the
         // ring slots of steps up to s0 + kRing - 2) are in place
         __syncthreads();
@@ -1000,8 +1122,9 @@ static hipError_t allow_lds(const void* kernel, size_t lds, size_t (&set)[kMaxDe
 
 // ------------------------------------------------------------- tile table
 
-// Every shape exists for both operand types; KCH is the channel block in
-// MFMA K chunks (bf16: 32 channels, fp32: 16 channels per chunk).
+// Shapes 0..19, 27 and 28 exist for fp32 and bf16 operands, 20..26 for bf16,
+// and those that tile_exists() names for three planes; KCH is the channel block
+// in MFMA K chunks (fp32: 16 channels, else 32 channels per chunk).
 static const TileShape kTiles[] = {
     // MB NB WGM WGN WGK KCH
     {1, 1, 1, 1, 4, 4},    // 0: 16x16, K in 4 partitions across waves
@@ -1034,18 +1157,30 @@ static const TileShape kTiles[] = {
     {1, 4, 4, 1, 1, 4, 1}, // 26: 64x64
     {2, 2, 1, 1, 4, 8},    // 27: 32x32, 4 partitions, 8-chunk channel block
     {2, 2, 4, 1, 1, 2},    // 28: 128x32, for outputs of at most 32 columns
+    // two K partitions (three planes)
+    {1, 2, 2, 1, 2, 2},    // 29: 32x32
+    {2, 1, 2, 1, 2, 2},    // 30: 64x16
+    {2, 2, 2, 1, 2, 2},    // 31: 64x32
 };
 
 int num_tile_variants() { return (int)(sizeof(kTiles) / sizeof(kTiles[0])); }
 TileShape tile_variant(int v) { return kTiles[v]; }
 
-size_t conv_lds_bytes(int v, bool bf16, const ConvParams& p)
+bool tile_exists(int v, int op)
+{
+    const TileShape& t = kTiles[v];
+    if (op == kOpBF16) return t.WGK != 2;
+    if (op == kOpF32) return t.WGK != 2 && !t.W;
+    return v == 0 || v == 3 || v == 5 || v == 6 || v == 9 || v >= 29;
+}
+
+size_t conv_lds_bytes(int v, int op, const ConvParams& p)
 {
     const TileShape& t = kTiles[v];
     const int rows = t.BM() + (p.k - 1) * p.d;
-    const int pad = bf16 ? OpT<true>::PAD : OpT<false>::PAD;
-    const int cb = t.KCH * (bf16 ? OpT<true>::KQ : OpT<false>::KQ);
-    const size_t a = (size_t)rows * (cb + pad) * (bf16 ? 2 : 4) * (bf16 && p.split ? 2 : 1);
+    const size_t row = op == kOpF32 ? (size_t)(t.KCH * OpT<kOpF32>::KQ + OpT<kOpF32>::PAD) * 4
+                                    : (size_t)(t.KCH * OpT<kOpBF16>::KQ + OpT<kOpBF16>::PAD) * 2;
+    const size_t a = rows * row * (op == kOpX3 ? 3 : op == kOpBF16 && p.split ? 2 : 1);
     if (t.W) return (size_t)kRing * (t.BN() / 16) * 1024 + a;
     const size_t red = t.WGK > 1 ? (size_t)t.S() * t.BM() * t.BN() * 4 : 0;
     return a > red ? a : red;
@@ -1063,6 +1198,34 @@ static hipError_t launch_t(const ConvGroup& g, int count, size_t lds, hipStream_
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((conv_kernel<BF16, MB, NB, WGM, WGN, WGK, KCH>), grid, dim3(256), lds, st, g);
     return hipGetLastError();
+}
+
+template <int MB, int NB, int WGM, int WGN, int WGK, int KCH>
+static hipError_t launch_x(const ConvGroup& g, int count, size_t lds, hipStream_t st)
+{
+    constexpr int BN = 16 * NB * WGN;
+    const ConvParams& p = g.p;
+    dim3 grid((unsigned)(p.B * p.tiles_t), (unsigned)((p.N + BN - 1) / BN), (unsigned)count);
+    static size_t lds_set[kMaxDevices] = {};
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(&xconv_kernel<MB, NB, WGM, WGN, WGK, KCH>), lds, lds_set);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((xconv_kernel<MB, NB, WGM, WGN, WGK, KCH>), grid, dim3(256), lds, st, g);
+    return hipGetLastError();
+}
+
+static hipError_t launch_x3(int v, const ConvGroup& g, int count, size_t lds, hipStream_t st)
+{
+    switch (v) {
+    case 0: return launch_x<1, 1, 1, 1, 4, 4>(g, count, lds, st);
+    case 3: return launch_x<1, 2, 1, 1, 4, 4>(g, count, lds, st);
+    case 5: return launch_x<2, 2, 1, 1, 4, 4>(g, count, lds, st);
+    case 6: return launch_x<1, 1, 2, 2, 1, 2>(g, count, lds, st);
+    case 9: return launch_x<2, 2, 2, 2, 1, 2>(g, count, lds, st);
+    case 29: return launch_x<1, 2, 2, 1, 2, 2>(g, count, lds, st);
+    case 30: return launch_x<2, 1, 2, 1, 2, 2>(g, count, lds, st);
+    case 31: return launch_x<2, 2, 2, 1, 2, 2>(g, count, lds, st);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <int MB, int NB, int WGM, int WGN, int KCH>
@@ -1133,20 +1296,21 @@ static bool same_shape(const ConvParams& a, const ConvParams& b)
            a.mean[0] == b.mean[0] && a.mean[1] == b.mean[1] && a.mean[2] == b.mean[2]));
 }
 
-hipError_t launch_conv(int v, bool bf16, const ConvParams* ps, int count, hipStream_t st)
+hipError_t launch_conv(int v, int op, const ConvParams* ps, int count, hipStream_t st)
 {
     if (count < 1 || count > kMaxGroup) return hipErrorInvalidValue;
     ConvGroup g{};
     g.p = ps[0];
-    size_t lds = conv_lds_bytes(v, bf16, ps[0]);
+    size_t lds = conv_lds_bytes(v, op, ps[0]);
     for (int i = 1; i < count; i++) {
         if (!same_shape(ps[0], ps[i])) return hipErrorInvalidValue;
         g.m[i - 1] = ConvMember{ps[i].in, ps[i].in_R, ps[i].wp, ps[i].bias, ps[i].out,
                                 ps[i].out_R, ps[i].res, ps[i].res_R, ps[i].k};
-        const size_t l = conv_lds_bytes(v, bf16, ps[i]);
+        const size_t l = conv_lds_bytes(v, op, ps[i]);
         lds = l > lds ? l : lds;
     }
-    return bf16 ? launch_dt<true>(v, g, count, lds, st) : launch_dt<false>(v, g, count, lds, st);
+    if (op == kOpX3) return launch_x3(v, g, count, lds, st);
+    return op == kOpBF16 ? launch_dt<true>(v, g, count, lds, st) : launch_dt<false>(v, g, count, lds, st);
 }
 
 // ------------------------------------------------------ fused resblock pair
@@ -1196,7 +1360,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     constexpr int KQ = 32;
     constexpr int C = KQ * KCH;
     constexpr int BM = 16 * MB * WGM, BN = 16 * NB * WGN;
-    constexpr int LDW = C + OpT<true>::PAD;
+    constexpr int LDW = C + OpT<kOpBF16>::PAD;
     constexpr int VPR = C / 8;                 // 8-channel groups per frame
     constexpr int ZM = (1 << LZ) - 1, HM = (1 << LH) - 1;
     static_assert(WGM * WGN == 4 && BN == C, "pair tile shape");
@@ -1519,7 +1683,7 @@ PairShape pair_variant(int v) { return kPairs[v]; }
 size_t pair_lds_bytes(int v)
 {
     const PairShape& t = kPairs[v];
-    return (size_t)(t.WZ() + t.WH()) * (t.C() + OpT<true>::PAD) * 2;
+    return (size_t)(t.WZ() + t.WH()) * (t.C() + OpT<kOpBF16>::PAD) * 2;
 }
 
 template <int MB, int NB, int WGM, int WGN, int KCH, int LZ, int LH>

@@ -43,6 +43,9 @@ struct ConvOp {
     int in_act = 0, out_act = 0;
     bool bf16 = false;   // operand type
     bool split = false;  // bf16 operand as a hi + lo pair
+    bool x3 = false;     // fp32 operands as three bf16 planes
+    int kind() const { return bf16 ? kOpBF16 : x3 ? kOpX3 : kOpF32; }
+    int kq() const { return kind() == kOpF32 ? 16 : 32; }   // channels of an MFMA K chunk
     bool transposed = false;
     size_t w_off = 0, b_off = 0, w_bytes = 0;
     size_t blob_w = 0, blob_b = 0;  // float offsets into the blob
@@ -221,7 +224,7 @@ static std::string validate(const dc_cfg* c)
     if (c->flags & ~(uint32_t)(DC_HOST_PTRS | DC_NO_GRAPH | DC_NO_FUSE | DC_FLUSH_CATALOG | DC_NO_RING))
         return "unknown flag bits";
     if ((c->flags & DC_FLUSH_CATALOG) && (c->flags & DC_NO_GRAPH)) return "DC_FLUSH_CATALOG needs graphs (not DC_NO_GRAPH)";
-    if (c->tile_variant < 0 || c->tile_variant > num_tile_variants()) return "tile_variant out of range";
+    if (c->tile_variant < 0 || c->tile_variant > kForcedTiles) return "tile_variant out of range";
     if (c->n_harmonics < 0 || c->n_harmonics >= kMaxSinusoidsHost) return "n_harmonics must be in [0, 31]";
     if (c->n_harmonics > 0) {
         if (!(c->sine_amp >= 0.0f && c->sine_amp < 1e6f) || !(c->noise_std >= 0.0f && c->noise_std < 1e6f))
@@ -236,11 +239,11 @@ static std::string validate(const dc_cfg* c)
 // block CB = K quantum x KCH channels, ceil(Ci / CB) blocks (zero padded).
 static void set_blocks(ConvOp& op)
 {
-    const int kq = op.bf16 ? 32 : 16;
+    const int kq = op.kq();
     op.CB = kq * tile_variant(op.variant).KCH;
     op.n_cb = (op.Ci + op.CB - 1) / op.CB;
     op.NB16 = (op.N + 15) / 16;
-    op.w_bytes = (size_t)op.n_cb * op.k * (op.CB / kq) * op.NB16 * 64 * 16;
+    op.w_bytes = (size_t)op.n_cb * op.k * (op.CB / kq) * op.NB16 * 64 * 16 * (op.x3 ? 3 : 1);
 }
 
 // Weight value of column n, input channel ch, tap j (0 outside the layer).
@@ -254,10 +257,35 @@ static float weight_at(const ConvOp& op, const float* blob, int n, int ch, int j
     return blob[op.blob_w + ((size_t)ch * op.out_C + o) * (2 * op.u) + r + (1 - j) * op.u];
 }
 
-// Pack into MFMA fragment order: [cb][tap][chunk][col block][lane][values].
+// w = hi + mid + lo, each the nearest bfloat16 of what is left (the last is
+// exact; a magnitude past bfloat16 is cut instead of rounded).
+static inline void split3(float w, uint16_t (&h)[3])
+{
+    uint32_t u;
+    std::memcpy(&u, &w, 4);
+    if ((u & 0x7fffffffu) >= 0x7f7f8000u) {   // an infinity or NaN, or rounds to one
+        const bool fin = (u & 0x7f800000u) != 0x7f800000u;
+        h[0] = fin ? (uint16_t)(u >> 16) : host_f2bf(w);
+        w = fin ? w - host_bf2f(h[0]) : 0.0f;
+        h[1] = host_f2bf(w);
+        h[2] = host_f2bf(w - host_bf2f(h[1]));
+        return;
+    }
+    for (int q = 0; q < 3; q++) {
+        std::memcpy(&u, &w, 4);
+        u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+        h[q] = (uint16_t)(u >> 16);
+        float f;
+        std::memcpy(&f, &u, 4);
+        w -= f;
+    }
+}
+
+// Pack into MFMA fragment order: [cb][tap][chunk][col block][lane][values];
+// three planes: [cb][tap][chunk][col block][plane][lane][values].
 static void pack_weights(const ConvOp& op, const float* blob, bool round_bf16, char* dst)
 {
-    const int kq = op.bf16 ? 32 : 16;
+    const int kq = op.kq();
     const int chunks = op.CB / kq;
     size_t idx = 0;
     for (int cb = 0; cb < op.n_cb; cb++)
@@ -266,7 +294,14 @@ static void pack_weights(const ConvOp& op, const float* blob, bool round_bf16, c
                 for (int nb = 0; nb < op.NB16; nb++)
                     for (int lane = 0; lane < 64; lane++) {
                         const int n = nb * 16 + (lane & 15);
-                        if (op.bf16) {
+                        if (op.x3) {
+                            uint16_t* o = (uint16_t*)dst + (idx / 64 * 3 * 64 + lane) * 8;
+                            for (int e = 0; e < 8; e++) {
+                                uint16_t h[3];
+                                split3(weight_at(op, blob, n, cb * op.CB + kc * 32 + (lane >> 4) * 8 + e, j), h);
+                                for (int q = 0; q < 3; q++) o[q * 64 * 8 + e] = h[q];
+                            }
+                        } else if (op.bf16) {
                             uint16_t* o = (uint16_t*)dst + idx * 8;
                             for (int e = 0; e < 8; e++) {
                                 const int ch = cb * op.CB + kc * 32 + (lane >> 4) * 8 + e;
@@ -307,9 +342,9 @@ static bool variant_fits(const ConvOp& op, int v)
     p.d = op.d;
     p.split = op.split;
     const TileShape t = tile_variant(v);
-    if (t.W && !op.bf16) return false;   // the LDS weight ring exists for bf16 operands only
+    if (!tile_exists(v, op.kind())) return false;
     const int npad = (op.N + 15) / 16 * 16;
-    return conv_lds_bytes(v, op.bf16, p) <= 80 * 1024 && t.BN() <= (npad > 16 ? npad : 16);
+    return conv_lds_bytes(v, op.kind(), p) <= 80 * 1024 && t.BN() <= (npad > 16 ? npad : 16);
 }
 
 // Shapes with the weight fragments in an LDS ring (bf16, one K partition),
@@ -343,9 +378,11 @@ static int pick_variant(const dc_state* s, const ConvOp& op)
         // fitting shape with the same arithmetic (K partitions, channel block)
         const int fv = s->cfg.tile_variant - 1;
         if (variant_fits(op, fv)) return fv;
+        // (three planes: with the same K partitions, whose shapes share one channel block)
+        const int kch = op.x3 ? (tile_variant(fv).WGK == 4 ? 4 : 2) : tile_variant(fv).KCH;
         int best = -1;
         for (int v = 0; v < nv; v++)
-            if (tile_variant(v).WGK == tile_variant(fv).WGK && tile_variant(v).KCH == tile_variant(fv).KCH &&
+            if (tile_variant(v).WGK == tile_variant(fv).WGK && tile_variant(v).KCH == kch &&
                 variant_fits(op, v) && (best < 0 || tile_variant(v).BM() * tile_variant(v).BN() >
                                                         tile_variant(best).BM() * tile_variant(best).BN()))
                 best = v;
@@ -366,9 +403,13 @@ static int pick_variant(const dc_state* s, const ConvOp& op)
         const int bm = t.BM();
         return (double)F / (double)(((F + bm - 1) / bm) * bm);
     };
-    const int kq = op.bf16 ? 32 : 16;
+    const int kq = op.kq();
     const int kch_all = (op.Ci + kq - 1) / kq;      // chunks covering every input channel
-    const int wgk = B < DC_BATCHED_MIN ? 4 : 1;
+    // (three planes of fewer than 128 channels: two partitions, for their two
+    // chunks of 32; 64 channels at B=1, n=25: 13 us a launch, four 18.5.  With
+    // 128 or more two measured slower at B=1, 16.2 us against 13.0, and equal at
+    // B=5, n=13: 28 and 29.)
+    const int wgk = B >= DC_BATCHED_MIN ? 1 : op.x3 && kch_all < 4 ? 2 : 4;
     // channel-block candidates, widest first: no wider than the channels
     // (nor than 4 chunks when waves do not split K)
     for (int kch = 32; kch >= 1; kch /= 2) {
@@ -378,13 +419,13 @@ static int pick_variant(const dc_state* s, const ConvOp& op)
         // most 128 channels.  The 256-channel stage's widest tile then stages
         // 34 KB instead of 68 KB, four blocks fit a CU instead of two, and its
         // grouped launches run in about one round of blocks instead of two.
-        if (wgk == 4 && !op.bf16 && op.stage >= 0 && kch > 8) continue;
+        if (wgk == 4 && op.kind() == kOpF32 && op.stage >= 0 && kch > 8) continue;
         // fp32 K-split convs of 256 channels or more with a 50-row left
         // context (the 256-channel stage at dilation 5): 16x32 tiles, so the
         // 66 staged rows serve 32 columns per block instead of 16 (the
         // grouped launch measured 24.9 -> 21.7 us; the 128-channel stage's
         // 32x32 tiles stay, where 16x32 measured slower)
-        if (wgk == 4 && !op.bf16 && op.Ci >= 256 && (op.k - 1) * op.d >= 50) {
+        if (wgk == 4 && op.kind() == kOpF32 && op.Ci >= 256 && (op.k - 1) * op.d >= 50) {
             for (int v = 0; v < nv; v++) {
                 const TileShape t = tile_variant(v);
                 if (t.WGK == 4 && t.KCH == kch && t.MB == 1 && t.NB == 2 && t.WGM == 1 && t.WGN == 1 && variant_fits(op, v))
@@ -431,18 +472,24 @@ static int pick_variant(const dc_state* s, const ConvOp& op)
         const bool bytes_heavy = op.res >= 0 || op.N <= 64;
         const int* pref = bytes_heavy ? kPrefer64 : kPreferLarge;
         const int npref = bytes_heavy ? (int)(sizeof(kPrefer64) / sizeof(int)) : (int)(sizeof(kPreferLarge) / sizeof(int));
-        const int* order = wgk == 4 ? nullptr : pref;
-        for (int oi = 0; oi < (wgk == 4 ? nv : npref); oi++) {
+        const int* order = wgk > 1 ? nullptr : pref;
+        for (int oi = 0; oi < (wgk > 1 ? nv : npref); oi++) {
             const int v = order ? order[oi] : oi;
             const TileShape t = tile_variant(v);
             if (t.WGK != wgk || t.KCH != kch || !variant_fits(op, v)) continue;
             double score;
-            if (wgk == 4) {
+            if (wgk > 1) {
                 // waves of the whole launch (all its members) up to three per
                 // SIMD, then larger tiles: each wave's operands then serve
                 // more MFMAs and the layer's weights are read by fewer blocks
-                const double waves = (double)(members * blocks(t)) * 4.0;
-                score = (waves < 3072.0 ? waves : 3072.0) * eff(t) * (1.0 + 0.1 * std::log2((double)(t.MB * t.NB)));
+                // (three planes: 768 waves, as larger tiles stage each frame's three
+                // planes and read its weights for more outputs -- 128 channels at
+                // B=1, n=25: 13.0 us in 32x32 tiles, 16x32 17.3, 16x16 18.9 --
+                // and of the branch-mean position only its own conv: 256
+                // channels there 10.5 us in 16x32 tiles, 32x32 15.2)
+                const double cap = op.x3 ? 768.0 : 3072.0;
+                const double waves = (double)((op.x3 && mean_pos ? 1 : members) * blocks(t)) * 4.0;
+                score = (waves < cap ? waves : cap) * eff(t) * (1.0 + 0.1 * std::log2((double)(t.MB * t.NB)));
             } else {
                 // the first shape in preference order that keeps enough blocks
                 // (a conv whose call fits in one row tile per stream -- the
@@ -576,6 +623,19 @@ static void build_network(dc_state* s)
         std::vector<int> zlast;
         int X = -1;
         const bool fuse = fuse_stage(c, co);
+        // an fp32 decoder's resblock convs of 64 channels or more, most of its
+        // work, as three bf16 planes; narrower ones, the pre-stack, the
+        // transposed convs and the head are bound by latency or by their weights'
+        // bytes (batch 1, us, fp32 MFMA against planes: pre-stack 6.3 and 7.3, the
+        // first transposed conv 9.3 and 12.8, the head 5.8 and 6.8; the tiny
+        // decoder's convs 3.7 and 4.4).  All of a stage's convs or none, as its
+        // branches share launches; contexts past 64 rows would not leave the planes
+        // of a tile room in LDS.
+        int halo = 0;
+        for (int j = 0; j < c.n_rb; j++)
+            for (int m = 0; m < c.n_dil; m++)
+                halo = std::max(halo, (c.rb_kernel[j] - 1) * std::max(1, (int)c.dil[m]));
+        const bool x3 = !bf && co >= 64 && halo <= 64;
         for (int j = 0; j < c.n_rb; j++) {
             const int kj = c.rb_kernel[j];
             int zin = Y;
@@ -590,6 +650,7 @@ static void build_network(dc_state* s)
                     op.branch = j;
                     op.dil_i = i;
                     op.half = 1;
+                    op.x3 = x3;
                     // fused: the pair reads z back far enough for both convs
                     need_ctx(s, zin, (kj - 1) * c.dil[i] + (fuse ? kj - 1 : 0));
                 }
@@ -609,6 +670,7 @@ static void build_network(dc_state* s)
                 op.branch = j;
                 op.dil_i = i;
                 op.half = 2;
+                op.x3 = x3;
                 if (fuse) op.partner = (int)s->convs.size() - 2;
                 need_ctx(s, H, kj - 1);
                 if (Z == X) {
@@ -905,7 +967,7 @@ static hipError_t launch_layer(dc_state* s, int i, int n, hipStream_t st, double
         const int cnt = (int)la.convs.size();
         for (int m = 0; m < cnt; m++) ps[m] = conv_params(s, s->convs[la.convs[m]], n);
         const ConvOp& op = s->convs[la.convs[0]];
-        return launch_conv(op.variant, op.bf16, ps, cnt, st);
+        return launch_conv(op.variant, op.kind(), ps, cnt, st);
     }
     case L_PAIR: {
         PairParams ps[kMaxGroup];
@@ -1727,8 +1789,8 @@ dc_status dc_layer_info_get(const dc_state* s, int32_t i, dc_layer_info* out)
             set("dc::wconv_kernel<" + std::to_string(t.MB) + ", " + std::to_string(t.NB) + ", " +
                 std::to_string(t.WGM) + ", " + std::to_string(t.WGN) + ", " + std::to_string(t.KCH) + ">");
         else
-            set("dc::conv_kernel<" + std::string(op0.bf16 ? "true" : "false") + ", " + std::to_string(t.MB) + ", " +
-                std::to_string(t.NB) + ", " + std::to_string(t.WGM) + ", " + std::to_string(t.WGN) + ", " +
+            set((op0.x3 ? "dc::xconv_kernel<" : op0.bf16 ? "dc::conv_kernel<true, " : "dc::conv_kernel<false, ") +
+                std::to_string(t.MB) + ", " + std::to_string(t.NB) + ", " + std::to_string(t.WGM) + ", " + std::to_string(t.WGN) + ", " +
                 std::to_string(t.WGK) + ", " + std::to_string(t.KCH) + ">");
         for (int ci : la.convs) {   // the members' work and compulsory bytes add up
             const ConvOp& op = s->convs[ci];
@@ -1739,7 +1801,7 @@ dc_status dc_layer_info_get(const dc_state* s, int32_t i, dc_layer_info* out)
             out->cols = op.N;
             out->depth += (int64_t)op.k * op.Ci;
             out->flops += 2.0 * B * F * op.N * op.Ci * op.k;
-            const double wes = op.bf16 ? 2 : 4;
+            const double wes = op.bf16 ? 2 : op.x3 ? 6 : 4;
             const double ies = elem_bytes(in.elem), oes = elem_bytes(o.elem);
             const double Fo = F * op.u;
             out->bytes += (double)op.N * op.Ci * op.k * wes + B * (F + (op.k - 1) * op.d) * op.Ci * ies +

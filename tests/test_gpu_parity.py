@@ -383,3 +383,35 @@ def _hip_copy(dst: int, src: int, nbytes: int):
     hip = ctypes.CDLL("libamdhip64.so")
     hip.hipMemcpy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
     assert hip.hipMemcpy(dst, src, nbytes, 4) == 0   # hipMemcpyDefault
+
+
+@pytest.mark.parametrize("C,rb_kernel,dil,planes", [
+    (64, [3], [1], True),            # two chunks of 32 channels, two K partitions
+    (96, [3, 7], [1, 5], True),      # three chunks in blocks of two
+    (128, [3, 7, 11], [1, 3], True),
+    (264, [3, 7], [1], True),        # a last channel block and column tile nearly empty
+    (128, [9], [1, 8], True),        # a 64-row context, the widest
+    (64, [7], [1, 11], False),       # 66 rows: fp32 MFMA
+    (48, [3], [1], False),
+])
+def test_f32_planes_edges_match_oracle(C, rb_kernel, dil, planes):
+    """fp32 resblock convs as three bf16 planes: channel counts and contexts at
+    the edges of the rule, ragged calls, against the oracle; a stream's bits do
+    not depend on the chunking or on the batch within a class."""
+    arch = dict(TINY, n_pre=1, up_rate=[2, 2], channels=[64, C, 64], rb_kernel=rb_kernel, dil=dil)
+    blob = synth.make_weights(arch, 3)
+    ids = synth.make_tokens(arch, 9, 26)
+    sizes = [13, 1, 12]
+    for B in (1, 7, 9):
+        dec = dc.Decoder(arch, "f32", blob, batch=B, chunk_tokens=13, max_tokens=26)
+        kernels = [l["kernel"] for l in dec.layers() if l["name"].startswith("s0.rb")]
+        assert kernels and all(k.startswith("dc::xconv_kernel") == planes for k in kernels), kernels
+        pcm = decode_chunks(dec, ids[:B], sizes)
+        dec.reset()
+        assert bits_equal(pcm, decode_chunks(dec, ids[:B], [26]))
+        dec.close()
+        check_oracle(arch, "f32", blob, ids[B - 1:B], pcm[B - 1:], f"f32 planes C={C} B={B}")
+        if B == 1:
+            one = pcm
+        elif B == 7:
+            assert bits_equal(pcm[:1], one)
