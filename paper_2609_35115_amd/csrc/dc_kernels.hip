@@ -538,6 +538,18 @@ __device__ __forceinline__ void store_tile(const ConvParams& p, const OutRef& rs
 template <int OP, int MB, int NB, int WGM, int WGN, int WGK, int KCH>
 __device__ __forceinline__ void conv_body(const ConvGroup& g)
 {
+    int bx = blockIdx.x, by = blockIdx.y;
+    if constexpr (OP == kOpX3) {
+        // Blocks go to the 8 XCDs round robin by their linear index: each XCD's
+        // blocks of a branch take one contiguous run of its tiles, rows first, so
+        // few column blocks' weights, 6 bytes a value, pass through its L2 (us per
+        // launch at batch 1, n = 25, 256 channels: 17.2 -> 15.0; 128 channels and
+        // fewer the same).
+        const unsigned nx = gridDim.x, total = nx * gridDim.y, id = bx + nx * by, xcd = id & 7;
+        const unsigned t = xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
+        by = (int)(t / nx);
+        bx = (int)(t % nx);
+    }
     constexpr bool BF16 = OP == kOpBF16, X3 = OP == kOpX3;
     // shared fields from member 0; this block's member supplies the rest
     const ConvParams& p = g.p;
@@ -576,9 +588,9 @@ __device__ __forceinline__ void conv_body(const ConvGroup& g)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: scalar index math
     const int wk = wave % WGK, wm = (wave / WGK) % WGM, wn = wave / (WGK * WGM);
-    const int b = blockIdx.x / p.tiles_t;
-    const int t0 = (blockIdx.x - b * p.tiles_t) * BM;
-    const int n0 = blockIdx.y * BN;
+    const int b = bx / p.tiles_t;
+    const int t0 = (bx - b * p.tiles_t) * BM;
+    const int n0 = by * BN;
     const int halo = (k - 1) * p.d;
     const int rows = BM + halo;
     const int64_t tau0 = p.clock[0] * p.in_fpt;
@@ -922,9 +934,10 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvGroup)
 // and, in the 256-channel stage, by reading its weights (6 bytes each, 50 MB
 // over its launches), with more streams by L2's weight stream again: tiles are
 // as large as leaves each SIMD a wave.  Us per launch of the three branches,
-// fp32 MFMA and planes, dilation 1: batch 1, n = 25, 256 channels 18.3 and 17.4,
-// 128 channels 18.5 and 12.6, 64 channels 16.3 and 12.5; batch 5, n = 25, 75.8
-// and 41.3, 78.4 and 47.0, 59.9 and 39.5.
+// fp32 MFMA and planes, dilation 1: batch 1, n = 25, 256 channels 18.3 and 15.0,
+// 128 channels 18.5 and 12.6, 64 channels 16.3 and 12.7; batch 5, n = 25, 75.8
+// and 38.5, 78.4 and 44.2, 59.9 and 36.1.  (A third tap buffer of weights:
+// slower, 15.0 -> 16.2 and 12.6 -> 13.4 at batch 1.)
 template <int MB, int NB, int WGM, int WGN, int WGK, int KCH>
 __global__ __launch_bounds__(256) void xconv_kernel(const ConvGroup)
 {
