@@ -219,6 +219,7 @@ def measured_peaks():
         y = torch.randn(m, m, device="cuda").to(dt)
         out[name] = round(2 * m ** 3 / best(lambda: torch.mm(x, y), reps) / 1e12, 1)
         del x, y
+    out["f32x3_gemm_TFLOPs"] = round(out["bf16_gemm_TFLOPs"] / 6, 1)   # six bf16 products per fp32 one
     torch.cuda.empty_cache()
     return out
 
