@@ -363,7 +363,7 @@ static const int kWideHaloTile = 14;
 // for another chunk size, or an offline state holding a whole utterance,
 // computes the same bits.  First the K partitions: 4 (waves split K) for the
 // streaming class (batch below DC_BATCHED_MIN), whose calls leave too few
-// output tiles to fill the machine, else 1.  Then the channel block:
+// output tiles to fill the machine (2 for narrow convs of three planes), else 1.  Then the channel block:
 // as wide as the layer's channels (capped at 4 chunks for unsplit tiles),
 // so no K step is padding.  Then the tile: for split K the largest that still
 // gives the launch about three waves per SIMD, otherwise the first in
@@ -415,8 +415,9 @@ static int pick_variant(const dc_state* s, const ConvOp& op)
     for (int kch = 32; kch >= 1; kch /= 2) {
         if (kch > kch_all && kch > 1) continue;
         if (wgk == 1 && kch > 4) continue;
-        // fp32 resblock convs of the streaming class: channel blocks of at
-        // most 128 channels.  The 256-channel stage's widest tile then stages
+        // fp32 resblock convs of the streaming class (those with contexts too
+        // wide for three planes): channel blocks of at most 128 channels.  The
+        // 256-channel stage's widest tile then stages
         // 34 KB instead of 68 KB, four blocks fit a CU instead of two, and its
         // grouped launches run in about one round of blocks instead of two.
         if (wgk == 4 && op.kind() == kOpF32 && op.stage >= 0 && kch > 8) continue;
