@@ -258,26 +258,38 @@ static float weight_at(const ConvOp& op, const float* blob, int n, int ch, int j
 }
 
 // w = hi + mid + lo, each the nearest bfloat16 of what is left (the last is
-// exact; a magnitude past bfloat16 is cut instead of rounded).
-static inline void split3(float w, uint16_t (&h)[3])
+// exact; a magnitude past bfloat16 is cut instead of rounded), of eight
+// weights at once: h[8 q + e] is plane q of w[e].
+static void split3x8(const float (&w)[8], uint16_t (&h)[24])
 {
-    uint32_t u;
-    std::memcpy(&u, &w, 4);
-    if ((u & 0x7fffffffu) >= 0x7f7f8000u) {   // an infinity or NaN, or rounds to one
-        const bool fin = (u & 0x7f800000u) != 0x7f800000u;
-        h[0] = fin ? (uint16_t)(u >> 16) : host_f2bf(w);
-        w = fin ? w - host_bf2f(h[0]) : 0.0f;
-        h[1] = host_f2bf(w);
-        h[2] = host_f2bf(w - host_bf2f(h[1]));
-        return;
+    uint32_t big = 0;
+    float rest[8];
+    for (int e = 0; e < 8; e++) {
+        uint32_t u;
+        std::memcpy(&u, &w[e], 4);
+        rest[e] = w[e];
+        big |= (u & 0x7fffffffu) >= 0x7f7f8000u;   // an infinity or NaN, or rounds to one
     }
-    for (int q = 0; q < 3; q++) {
-        std::memcpy(&u, &w, 4);
-        u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
-        h[q] = (uint16_t)(u >> 16);
-        float f;
-        std::memcpy(&f, &u, 4);
-        w -= f;
+    for (int q = 0; q < 3; q++)
+        for (int e = 0; e < 8; e++) {
+            uint32_t u;
+            std::memcpy(&u, &rest[e], 4);
+            u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+            h[8 * q + e] = (uint16_t)(u >> 16);
+            float f;
+            std::memcpy(&f, &u, 4);
+            rest[e] -= f;
+        }
+    if (!big) return;
+    for (int e = 0; e < 8; e++) {
+        uint32_t u;
+        std::memcpy(&u, &w[e], 4);
+        const bool fin = (u & 0x7f800000u) != 0x7f800000u;
+        if ((u & 0x7fffffffu) < 0x7f7f8000u) continue;
+        h[e] = fin ? (uint16_t)(u >> 16) : host_f2bf(w[e]);
+        const float r = fin ? w[e] - host_bf2f(h[e]) : 0.0f;
+        h[8 + e] = host_f2bf(r);
+        h[16 + e] = host_f2bf(r - host_bf2f(h[8 + e]));
     }
 }
 
@@ -296,11 +308,12 @@ static void pack_weights(const ConvOp& op, const float* blob, bool round_bf16, c
                         const int n = nb * 16 + (lane & 15);
                         if (op.x3) {
                             uint16_t* o = (uint16_t*)dst + (idx / 64 * 3 * 64 + lane) * 8;
-                            for (int e = 0; e < 8; e++) {
-                                uint16_t h[3];
-                                split3(weight_at(op, blob, n, cb * op.CB + kc * 32 + (lane >> 4) * 8 + e, j), h);
-                                for (int q = 0; q < 3; q++) o[q * 64 * 8 + e] = h[q];
-                            }
+                            float w[8];
+                            uint16_t h[24];
+                            for (int e = 0; e < 8; e++)
+                                w[e] = weight_at(op, blob, n, cb * op.CB + kc * 32 + (lane >> 4) * 8 + e, j);
+                            split3x8(w, h);
+                            for (int q = 0; q < 3; q++) std::memcpy(o + q * 64 * 8, h + 8 * q, 16);
                         } else if (op.bf16) {
                             uint16_t* o = (uint16_t*)dst + idx * 8;
                             for (int e = 0; e < 8; e++) {
