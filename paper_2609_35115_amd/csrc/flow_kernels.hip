@@ -919,6 +919,16 @@ struct AttnKeys {
     }
 };
 
+// Mask of an operand word's keys (two in bf16, one in fp32) that are the
+// segment's own, `left` of them from the word's first on.  The frames behind a
+// segment hold what an earlier call or turn left there, and a probability of
+// zero does not cancel an infinity or a NaN.
+template <bool BF16> __device__ __forceinline__ uint32_t own_keys(int left)
+{
+    if constexpr (BF16) return left >= 2 ? ~0u : left == 1 ? 0xffffu : 0u;
+    else return left >= 1 ? ~0u : 0u;
+}
+
 // Maximum over the lanes that differ in bits 4 and 5 (the four groups of 16).
 // (The swaps' results go through scalars: a bit cast straight from a vector's
 // element 1 reads element 0.)
@@ -945,10 +955,11 @@ __device__ __forceinline__ float max_xor16_32(float v)
 //     lane's eight probabilities are eight consecutive keys and its value
 //     operand is one 16-byte read.
 // What bounds it: HBM, the carried keys and values once: 269 MB per launch at
-// 128 streams in 67 us with the launch (4.3 TB/s; 106 us when the eight waves
+// 128 streams in 68 us with the launch (4.2 TB/s; 106 us when the eight waves
 // split the keys for all 64 queries and merged eight partial results, one
-// block of 140 KB LDS per CU).  At 16 streams, one block per CU, its eight
-// steps' latency: 14.8 us (17.9).
+// block of 140 KB LDS per CU; 67.2 without the mask over a segment's last
+// values).  At 16 streams, one block per CU, its eight steps' latency: 15.0 us
+// (17.9).
 template <bool BF16>
 __device__ __forceinline__ void attn_wide(const AttnParams& p)
 {
@@ -993,11 +1004,13 @@ __device__ __forceinline__ void attn_wide(const AttnParams& p)
     auto vplace = [](int d, int u) { return 32 * UK + d * UV + (u ^ (BF16 ? (d >> 2) & 3 : (d >> 1) & 7)); };
     struct Regs {
         u32x4 k[NLK], v[NLV];
+        int left;
     };
     auto load = [&](int step, Regs& r) {
         const int2 tl = tiles[min(2 * step + half, total - 1)];
         const int first = __builtin_amdgcn_readfirstlane(tl.x), left = __builtin_amdgcn_readfirstlane(tl.y);
         const int last = (left - 1) & ~(VE - 1);
+        r.left = left;
 #pragma unroll
         for (int i = 0; i < NLK; i++) {
             const int idx = lane + 64 * i, row = 8 * part + idx / UK, u = idx % UK;
@@ -1018,8 +1031,13 @@ __device__ __forceinline__ void attn_wide(const AttnParams& p)
         }
 #pragma unroll
         for (int i = 0; i < NLV; i++) {
-            const int idx = lane + 64 * i;
-            slot[vplace(16 * part + idx / UV, idx % UV)] = r.v[i];
+            const int idx = lane + 64 * i, u = idx % UV;
+            u32x4 v = r.v[i];
+            if (r.left < 32) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] &= own_keys<BF16>(r.left - VE * u - e * (VE / 4));
+            }
+            slot[vplace(16 * part + idx / UV, u)] = v;
         }
     };
 
@@ -1228,7 +1246,7 @@ __global__ __launch_bounds__(64 * NW, QG == 4 ? 4 : 1) void attn_kernel(const At
         }
     };
     // one tile: scores, running maximum and sum, O^T update
-    auto step = [&](const Tile& cur, int t0, int len, const QFrag& qfr, float& m, float& lsum, f32x4 (&O)[4]) {
+    auto step = [&](Tile& cur, int t0, int len, const QFrag& qfr, float& m, float& lsum, f32x4 (&O)[4]) {
         f32x4 st[2];
 #pragma unroll
         for (int j = 0; j < 2; j++) {
@@ -1273,6 +1291,19 @@ __global__ __launch_bounds__(64 * NW, QG == 4 ? 4 : 1) void attn_kernel(const At
         lsum = lsum * alpha + ps;
 #pragma unroll
         for (int db = 0; db < 4; db++) O[db] *= alpha;
+        if (len - t0 < 32) {   // values past the segment
+            const int left = len - t0 - 4 * g;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const uint32_t ma = own_keys<BF16>(left - (!BF16 ? e : e < 2 ? 2 * e : 12 + 2 * e));
+                const uint32_t mb = own_keys<BF16>(left - 16 - e);
+#pragma unroll
+                for (int db = 0; db < 4; db++) {
+                    cur.va[db][e] &= ma;
+                    if constexpr (!BF16) cur.vb[db][e] &= mb;
+                }
+            }
+        }
         if constexpr (BF16) {
             const u32x4 pw = {pack2(st[0][0], st[0][1]), pack2(st[0][2], st[0][3]), pack2(st[1][0], st[1][1]),
                               pack2(st[1][2], st[1][3])};
@@ -1297,7 +1328,7 @@ __global__ __launch_bounds__(64 * NW, QG == 4 ? 4 : 1) void attn_kernel(const At
     f32x4 O[4];
 #pragma unroll
     for (int db = 0; db < 4; db++) O[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto work = [&](int t, const Tile& cur) {
+    auto work = [&](int t, Tile& cur) {
         int base, len, t0;
         keys.locate(t, base, len, t0);
         step(cur, t0, len, qfr, m, lsum, O);

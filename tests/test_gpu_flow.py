@@ -381,6 +381,37 @@ def test_attention_scores_far_apart(B):
     dec.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B", [2, 32])   # the narrow and the wide attention
+def test_new_turn_ignores_what_a_turn_of_nan_left(dtype, B):
+    """The frames behind every segment still hold an earlier turn's keys and
+    values: after a turn whose features were not finite, new turns with shorter
+    prompts and calls (lengths with every remainder of 8 among them) give the
+    bits of a fresh decoder."""
+    a = dict(TINY, dim=64, heads=1, n_mel=8, depth=1, n_steps=2, f_prompt=40, f_retained=26, f_chunk=13, f_call=24)
+    blob = synth.make_flow_weights(a, 14)
+    flow = _flow()
+    dec = flow.FlowDecoder(a, dtype, blob, B, rng_seed=SEED)
+    mu = synth.make_flow_mu(a, B, 4 * a["f_chunk"] + a["f_call"])
+    mu_nan = np.full_like(mu, np.nan)
+    for plen, n in [(33, 24), (34, 18), (35, 19), (36, 20), (37, 21), (38, 22), (39, 23), (32, 1), (1, 5)]:
+        for b, pr in enumerate(_prompts(a, B, a["f_prompt"], seed=1)):
+            dec.prompt(b, np.full_like(pr[0], np.nan), *pr[1:])
+        for k in range(4):      # every slot of the ring
+            assert np.isnan(dec.decode(mu_nan[:, k * a["f_chunk"]:k * a["f_chunk"] + a["f_call"]]).cpu().numpy()).all()
+        prompts = _prompts(a, B, plen)
+        for b in range(B):
+            dec.prompt(b, *prompts[b])
+        ref, want, _, _ = _run_gpu(a, dtype, blob, B, plen, [n, n, n], prompts=prompts, mu=mu)
+        p = 0
+        for k, w in enumerate(want):
+            got = dec.decode(mu[:, p:p + n]).cpu().numpy()
+            p += a["f_chunk"] if n >= a["f_chunk"] else 0
+            assert np.isfinite(w).all() and bits_equal(got, w), f"prompt {plen}, call {k} of {n} frames"
+        ref.close()
+    dec.close()
+
+
 def test_real_shape_batch20_every_tile_size():
     """20 paper-shaped streams in bf16: 2,240 rows per call, so the MLP-up GEMM
     takes 128 x 128 tiles, the input, QKV, attention-output and MLP-down GEMMs
