@@ -347,7 +347,7 @@ ATTN_WIDE_BLOCKS = 64   # (stream, branch, head) x 64-query blocks from which at
 
 TILE_BIG_BLOCKS = 1024   # 64 x 64 tiles of a GEMM from which the tiled kernel takes 64 x 256 (4 waves)
 TILE_MID_BLOCKS = 256    # ... and from which it takes 64 x 256 (8 waves)
-SPLIT_K = 1024           # below both: K from which two K partitions run (whole chunks of 16 steps)
+BIG_K = 1024             # below both: K from which a plain operand takes 32 x 128, else 16 x 128
 
 
 def flow_kernel_name(role: str, dtype: str, rows: int, attn_blocks: int = 0, arch: dict | None = None) -> str:
@@ -367,8 +367,7 @@ def flow_kernel_name(role: str, dtype: str, rows: int, attn_blocks: int = 0, arc
                 waves, nblk, rb = (8 if K >= 1024 else 4), 1, 1
             return f"dcf::skinny_kernel<{b}, {epi}, {'true' if ln else 'false'}, {waves}, {nblk}, {rb}>"
         blocks = ((N + 63) // 64) * ((rows + 63) // 64)
-        steps = -(-K // (8 * (32 if dtype == "bf16" else 16))) * 8
-        small = "2, 2" if not ln and K >= SPLIT_K and steps % 16 == 0 else "1, 1"
+        small = "2, 1" if not ln and K >= BIG_K else "1, 1"
         tile = "4, 4" if blocks >= TILE_BIG_BLOCKS else "4, 2" if blocks >= TILE_MID_BLOCKS else small
         return f"dcf::gemm_kernel<{b}, {epi}, {tile}>"
     return f"dcf::{role}_kernel<{b}>" if role in ("assemble", "euler") else role

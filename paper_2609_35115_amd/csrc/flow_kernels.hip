@@ -166,10 +166,9 @@ __device__ __forceinline__ void epilogue4(const GemmParams& p, int row, int col,
 //     (the launch of its own that this took wrote and read the operand again);
 //   plain operand: K runs in chunks through two LDS buffers, the next chunk
 //     loaded into registers while this one is multiplied.
-// Every output element adds its K steps in ascending order (with K partitions:
-// each partition's, then the partial sums in wave order), and a row's
-// LayerNorm sums have one order, so a row's result does not depend on the tile
-// or the batch.
+// Every output element adds its K steps in ascending order, in one chain in
+// every tile, and a row's LayerNorm sums have one order, so a row's result does
+// not depend on the tile or, among calls of many rows, on the batch.
 // What bounds it: at 14,336 rows the weight stream from L2 (64 rows per
 // fragment, about 64 B/clk per CU at the full matrix rate) and the epilogue's
 // vector work; at 1,792 rows load latency and the rows' LayerNorm, which every
@@ -178,27 +177,22 @@ __device__ __forceinline__ void epilogue4(const GemmParams& p, int row, int col,
 // MLP up 95.3 -> 51.7, MLP down 55.4 -> 45.8; 1,792 rows 22.8 -> 16.8,
 // 22.7 -> 16.7, 20.7 -> 16.5.
 //
-// Waves of a block, and how many of them share its columns by splitting every
-// chunk of K between them.  8 waves halve how often rows are normalised and
-// weights read; 64 x 256-column tiles keep 4, since two such blocks per CU
-// run in different phases (QKV and MLP up at 14,336 rows: 44.3 and 51.7 us
-// with 4 waves, 63.0 and 59.9 with 8).  K >= 1024 runs 32 x 64 columns per
-// wave row with K in two partitions: twice the loads in flight per column
-// (MLP down at 1,792 rows: 16.5 us, against 17.7 without partitions and 20.7
-// with 16 x 64 tiles).
+// Waves of a block.  8 waves halve how often rows are normalised and weights
+// read; 64 x 256-column tiles keep 4, since two such blocks per CU run in
+// different phases (QKV and MLP up at 14,336 rows: 44.3 and 51.7 us with 4
+// waves, 63.0 and 59.9 with 8).
 template <int MB, int NB> constexpr int gemm_waves() { return MB == 4 && NB == 4 ? 4 : 8; }
-template <int MB, int NB> constexpr int gemm_ksplit() { return MB == 2 && NB == 2 ? 2 : 1; }
 
 // K values of an LDS row: the whole (padded) K of a LayerNorm operand, else a
-// chunk of kStepPad steps per K partition.
-template <bool BF16, bool LN, int KW> __host__ __device__ constexpr int panel_row(int KS)
+// chunk of kStepPad steps.
+template <bool BF16, bool LN> __host__ __device__ constexpr int panel_row(int KS)
 {
-    return (LN ? KS : KW * kStepPad) * (BF16 ? 32 : 16) + (BF16 ? 8 : 4);   // padded: conflict-free 16-byte reads
+    return (LN ? KS : kStepPad) * (BF16 ? 32 : 16) + (BF16 ? 8 : 4);   // padded: conflict-free 16-byte reads
 }
 
 template <int EPI> constexpr bool ln_operand() { return EPI == E_QKV || EPI == E_GELU || EPI == E_VEL; }
 
-constexpr int kSkinnyBigK = 1024;   // K from which a GEMM of a plain operand splits K further
+constexpr int kBigK = 1024;   // K from which a plain operand's GEMM takes more waves (few rows) or more rows a block
 
 // Where a row of the call goes (E_QKV): its q row, its carry region, its frame there.
 struct RowOut {
@@ -210,8 +204,6 @@ template <bool BF16, int EPI, int MB, int NB>
 __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(const GemmParams p)
 {
     constexpr int NW = gemm_waves<MB, NB>(), NT = 64 * NW;
-    constexpr int KW = ln_operand<EPI>() ? 1 : gemm_ksplit<MB, NB>(), NC = NW / KW;   // K partitions, column waves
-    constexpr int kChunk = KW * kStepPad;              // K steps of a plain operand's LDS buffer
     using T = typename std::conditional<BF16, uint16_t, float>::type;
     using Frag = typename std::conditional<BF16, bf16x8_t, f32x4>::type;
     constexpr bool LN = ln_operand<EPI>();
@@ -219,7 +211,7 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
     constexpr int KQ = BF16 ? 32 : 16, VE = BF16 ? 8 : 4;
     constexpr int D = NB >= 4 ? 4 : 8;                 // weight steps in flight
     extern __shared__ __align__(16) unsigned char smem[];
-    const int LD = panel_row<BF16, LN, KW>(p.KS);
+    const int LD = panel_row<BF16, LN>(p.KS);
     T* As = (T*)smem;                                  // [LN ? 1 : 2][BM][LD]
     float* ss = (float*)(As + (size_t)BM * LD);        // LN: scale, shift
     RowOut* ro = (RowOut*)(ss + 2 * p.K);              // E_QKV
@@ -228,14 +220,13 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
     const int l16 = lane & 15, g = lane >> 4;
     const int cs = blockIdx.x % p.nsplit, m0 = (blockIdx.x / p.nsplit) * BM;
     const int N16 = (p.N + 15) >> 4;
-    const int kw = wave / NC;                          // K partition: kStepPad steps of every chunk
-    const int cb0 = (cs * p.groups * NC + wave % NC) * NB;   // the wave's first column block; groups are NC NB apart
+    const int cb0 = (cs * p.groups * NW + wave) * NB;  // the wave's first column block; groups are NW NB apart
 
     const u32x4* Wl = (const u32x4*)p.W + lane;
     const u32x4* wn[NB];                               // fragments of the next steps to load
     auto aim = [&](int grp) {
 #pragma unroll
-        for (int j = 0; j < NB; j++) wn[j] = Wl + ((size_t)min(cb0 + grp * NC * NB + j, N16 - 1) * p.KS + kw * kStepPad) * 64;
+        for (int j = 0; j < NB; j++) wn[j] = Wl + ((size_t)min(cb0 + grp * NW * NB + j, N16 - 1) * p.KS) * 64;
     };
     u32x4 w[D][NB];
     auto load_w = [&](int i) {
@@ -246,13 +237,13 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
 #pragma unroll
     for (int i = 0; i < D; i++) load_w(i);
 
-    constexpr int NVA = (BM * kChunk * KQ / VE + NT - 1) / NT;   // a plain chunk's vectors per thread
-    constexpr int VPR = kChunk * KQ / VE;
+    constexpr int NVA = (BM * kStepPad * KQ / VE + NT - 1) / NT;   // a plain chunk's vectors per thread
+    constexpr int VPR = kStepPad * KQ / VE;
     u32x4 ra[NVA];
     auto gload = [&](int c) {
 #pragma unroll
         for (int v = 0; v < NVA; v++) {
-            const int idx = tid + NT * v, r = min(idx / VPR, BM - 1), k = c * kChunk * KQ + (idx % VPR) * VE;
+            const int idx = tid + NT * v, r = min(idx / VPR, BM - 1), k = c * kStepPad * KQ + (idx % VPR) * VE;
             const u32x4 x = *(const u32x4*)((const T*)p.A + (size_t)min(m0 + r, p.M - 1) * p.K + min(k, p.K - VE));
 #pragma unroll
             for (int e = 0; e < 4; e++) ra[v][e] = k < p.K ? x[e] : 0u;
@@ -390,7 +381,7 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
 
     if constexpr (LN) {
         for (int grp = 0; grp < p.groups; grp++) {
-            const int cb = cb0 + grp * NC * NB;
+            const int cb = cb0 + grp * NW * NB;
             clear();
             auto run = [&](auto rows_tag) {
                 for (int ks = 0; ks < p.KS; ks += D) {
@@ -478,35 +469,17 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
         }
     } else {
         clear();
-        const int nc = p.KS / kChunk;
+        const int nc = p.KS / kStepPad;
         for (int c = 0; c < nc; c++) {
             if (c + 1 < nc) gload(c + 1);
-            const T* a = a_lane + (size_t)(c & 1) * BM * LD + kw * kStepPad * KQ;
+            const T* a = a_lane + (size_t)(c & 1) * BM * LD;
 #pragma unroll
             for (int ks = 0; ks < kStepPad; ks += D) {
-                if (ks + D < kStepPad) ahead(D);
-                else if (c + 1 < nc) ahead(D + kChunk - kStepPad);
+                if (ks + D < kStepPad || c + 1 < nc) ahead(D);
                 steps(std::false_type{}, a + ks * KQ);
             }
             if (c + 1 < nc) lstore((c + 1) & 1);
             __syncthreads();
-        }
-        if constexpr (KW > 1) {   // (the chunks are done with)
-            f32x4* red = (f32x4*)smem;                 // [KW - 1][NC][MB * NB][64 lanes]
-            if (kw > 0) {
-#pragma unroll
-                for (int i = 0; i < MB; i++)
-#pragma unroll
-                    for (int j = 0; j < NB; j++) red[((wave - NC) * MB * NB + i * NB + j) * 64 + lane] = acc[i][j];
-            }
-            __syncthreads();
-            if (kw > 0) return;
-#pragma unroll
-            for (int w = 1; w < KW; w++)
-#pragma unroll
-                for (int i = 0; i < MB; i++)
-#pragma unroll
-                    for (int j = 0; j < NB; j++) acc[i][j] += red[(((w - 1) * NC + wave) * MB * NB + i * NB + j) * 64 + lane];
         }
 #pragma unroll
         for (int j = 0; j < NB; j++) {
@@ -550,12 +523,10 @@ template <bool BF16, int EPI, int MB, int NB>
 hipError_t launch_tiled(GemmParams p, hipStream_t st)
 {
     constexpr bool LN = ln_operand<EPI>();
-    constexpr int KW = LN ? 1 : gemm_ksplit<MB, NB>(), NC = gemm_waves<MB, NB>() / KW;
-    if (!LN && p.KS % (KW * kStepPad) != 0) return hipErrorInvalidValue;
-    const size_t rows = (size_t)16 * MB * panel_row<BF16, LN, KW>(p.KS) * (BF16 ? 2 : 4);
+    const size_t rows = (size_t)16 * MB * panel_row<BF16, LN>(p.KS) * (BF16 ? 2 : 4);
     const size_t lds = LN ? rows + (size_t)8 * p.K + (EPI == E_QKV ? 16 * MB * sizeof(RowOut) : 0) : 2 * rows;
-    static_assert((size_t)(KW - 1) * NC * MB * NB * 1024 <= (size_t)2 * 16 * MB * KW * kStepPad * 32, "partial sums fit the chunks");
-    const int tiles_m = (p.M + 16 * MB - 1) / (16 * MB), tiles_n = (p.N + 16 * NC * NB - 1) / (16 * NC * NB);
+    constexpr int BN = 16 * NB * gemm_waves<MB, NB>();
+    const int tiles_m = (p.M + 16 * MB - 1) / (16 * MB), tiles_n = (p.N + BN - 1) / BN;
     // a LayerNorm operand: one block per row tile normalises once for all its
     // column groups, as long as that leaves kGroupBlocks blocks
     p.nsplit = tiles_n;
@@ -572,8 +543,9 @@ hipError_t launch_tiled(GemmParams p, hipStream_t st)
 
 // Tile size by the number of 64 x 64 tiles the call would have: at least
 // DCF_TILE_BIG_BLOCKS -> 64 rows x 256 columns, at least DCF_TILE_MID_BLOCKS ->
-// 64 x 256 by 8 waves, fewer -> 16 x 128, or for K >= 1024 32 x 128 with two K
-// partitions (more blocks for calls that would not fill the machine).
+// 64 x 256 by 8 waves, fewer -> 16 x 128 (more blocks for calls that would not
+// fill the machine), or 32 x 128 for a plain operand of K >= 1024 (MLP down, us,
+// bf16: 1,792 rows 16.4, 16 x 128 20.7, 32 x 256 23.6; 560 rows 14.0).
 #ifndef DCF_TILE_BIG_BLOCKS
 #define DCF_TILE_BIG_BLOCKS 1024
 #endif
@@ -587,7 +559,8 @@ hipError_t launch_tiled_any(const GemmParams& p, hipStream_t st)
     const long small_blocks = (long)((p.N + 63) / 64) * ((p.M + 63) / 64);
     if (small_blocks >= DCF_TILE_BIG_BLOCKS) return launch_tiled<BF16, EPI, 4, 4>(p, st);
     if (small_blocks >= DCF_TILE_MID_BLOCKS) return launch_tiled<BF16, EPI, 4, 2>(p, st);
-    if (!ln_operand<EPI>() && p.K >= kSkinnyBigK && p.KS % (2 * kStepPad) == 0) return launch_tiled<BF16, EPI, 2, 2>(p, st);
+    if constexpr (!ln_operand<EPI>())
+        if (p.K >= kBigK) return launch_tiled<BF16, EPI, 2, 1>(p, st);
     return launch_tiled<BF16, EPI, 1, 1>(p, st);
 }
 
@@ -832,7 +805,7 @@ hipError_t launch_one(const GemmParams& p, hipStream_t st)
                 return launch_skinny<BF16, EPI, true, DCF_SK_LN_WAVES, DCF_SK_LN_NBLK, DCF_SK_LN_RB>(p, st);
             return launch_skinny<BF16, EPI, true, 4, DCF_SK_LN_NBLK, 1>(p, st);
         }
-        else if (p.K >= kSkinnyBigK)
+        else if (p.K >= kBigK)
             return launch_skinny<BF16, EPI, false, DCF_SK_BIGK_WAVES, DCF_SK_PLAIN_NBLK, DCF_SK_PLAIN_RB>(p, st);
         else
             return launch_skinny<BF16, EPI, false, DCF_SK_PLAIN_WAVES, DCF_SK_PLAIN_NBLK, DCF_SK_PLAIN_RB>(p, st);

@@ -69,6 +69,7 @@ def test_flow_kernel_names_follow_the_launch_rules():
     # batch 16 (1,792 rows): tiers by the number of 64 x 64 tiles
     assert name("gemm:fc1", "bf16", 1792, arch=a) == "dcf::gemm_kernel<true, 3, 4, 2>"   # 896 tiles
     assert name("gemm:o", "bf16", 1792, arch=a) == "dcf::gemm_kernel<true, 2, 1, 1>"     # 224 tiles
+    assert name("gemm:fc2", "bf16", 1792, arch=a) == "dcf::gemm_kernel<true, 2, 2, 1>"   # ... and K = 2048
     assert name("gemm:fc1", "bf16", 14336, arch=a) == "dcf::gemm_kernel<true, 3, 4, 4>"  # 7,168 tiles
     # attention: the wide shape from 64 blocks of 64 queries
     assert name("attn", "bf16", 112, attn_blocks=16) == "dcf::attn_kernel<true, 1, 4>"

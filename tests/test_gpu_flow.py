@@ -295,9 +295,9 @@ def test_many_rows_take_the_tiled_path_and_match_oracle(dtype):
 
 
 @pytest.mark.parametrize("dtype,dim,mlp,f_call,B", [
-    ("bf16", 64, 1056, 13, 24),    # K = 64 padded to 8 steps; n not a multiple of 4; K >= 1024 of an odd chunk count
+    ("bf16", 64, 1056, 13, 24),    # K = 64 padded to 8 steps; n not a multiple of 4; K >= 1024 that ends within a chunk
     ("f32", 64, 1056, 13, 24),
-    ("bf16", 192, 2048, 12, 27),   # a ragged last row tile; K = 2048 in two partitions; heads that straddle column groups
+    ("bf16", 192, 2048, 12, 27),   # a ragged last row tile; K = 2048; heads that straddle column groups
     ("f32", 192, 2048, 11, 27),
     ("bf16", 512, 1024, 13, 160),  # 4,160 rows: the widest tiles, several column groups per block
     ("f32", 512, 1024, 8, 260),
@@ -410,6 +410,23 @@ def test_new_turn_ignores_what_a_turn_of_nan_left(dtype, B):
             assert np.isfinite(w).all() and bits_equal(got, w), f"prompt {plen}, call {k} of {n} frames"
         ref.close()
     dec.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_bits_do_not_depend_on_the_batch_above_512_rows(dtype):
+    """Three batches whose GEMMs of K = 1024 and K = 512 take each of the many-row
+    tiles (832, 2,080 and 8,320 rows): a stream's bits are the same in all."""
+    a = dict(TINY, dim=512, heads=8, mlp=1024, n_mel=8, depth=1, n_steps=2, f_prompt=9, f_retained=8, f_chunk=8, f_call=13)
+    blob = synth.make_flow_weights(a, 16)
+    calls = [13, 13]
+    want = None
+    for B in (32, 80, 320):
+        dec, outs, _, _ = _run_gpu(a, dtype, blob, B, a["f_prompt"], calls)
+        dec.close()
+        if want is None:
+            want = outs
+        for k, (g, w) in enumerate(zip(outs, want)):
+            assert bits_equal(g[:32], w), f"batch {B}, call {k}"
 
 
 def test_real_shape_batch20_every_tile_size():
