@@ -279,7 +279,6 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
         constexpr int NV = 8;                          // K <= 512
         constexpr int NP = (BM + NT / 16 - 1) / (NT / 16);   // passes
         const int q = tid & 15, nv = p.K >> 6;
-        const float rK = 1.0f / (float)p.K;
         f32x4 x[NV], nx[NV];
         auto hload = [&](int mb, f32x4 (&v)[NV]) {
             const f32x4* hr = (const f32x4*)(p.ln_h + (size_t)min(m0 + mb * (NT / 16) + min(tid >> 4, BM - 1), p.M - 1) * p.K) + q;
@@ -291,7 +290,10 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
 #pragma unroll 1
         for (int mb = 0; mb < NP; mb++) {
             hload(min(mb + 1, NP - 1), nx);
-            // the row's first value (lane 0 of the DPP row: row_newbcast:0)
+            // the row's first value (lane 0 of the DPP row: row_newbcast:0).  The mean is
+            // subtracted before the scaling, as in the few-row kernel: folded into
+            // x rstd - mean rstd it is rounded twice (rows whose mean is 20 times their
+            // deviation: error of a solve 1.78e-6, folded 2.17e-6, at the same time).
             const float x0 = row_ror<0x150>(x[0][0]);
             float s1 = 0.f, s2 = 0.f;
 #pragma unroll
@@ -306,8 +308,8 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
                 }
             s1 = row_sum(s1);
             s2 = row_sum(s2);
-            const float md = s1 * rK;
-            const float rstd = 1.0f / sqrtf(fmaxf(s2 * rK - md * md, 0.f) + 1e-6f), c0 = -(x0 + md) * rstd;
+            const float md = s1 / (float)p.K;
+            const float mean = x0 + md, rstd = 1.0f / sqrtf(fmaxf(s2 / (float)p.K - md * md, 0.f) + 1e-6f);
             const int r = mb * (NT / 16) + (tid >> 4);
             T* row = As + (size_t)r * LD;
             if (r < BM) {
@@ -318,7 +320,7 @@ __global__ __launch_bounds__((64 * gemm_waves<MB, NB>()), 2) void gemm_kernel(co
                     const f32x4 sc = *(const f32x4*)(ss + k), sh = *(const f32x4*)(ss + p.K + k);
                     f32x4 a;
 #pragma unroll
-                    for (int e = 0; e < 4; e++) a[e] = fmaf(fmaf(x[i][e], rstd, c0), sc[e], sh[e]);
+                    for (int e = 0; e < 4; e++) a[e] = fmaf((x[i][e] - mean) * rstd, sc[e], sh[e]);
                     store4<BF16>(row, k, a);
                 }
             for (int k = p.K + 4 * q; k < p.KS * KQ; k += 64) store4<BF16>(row, k, f32x4{0.f, 0.f, 0.f, 0.f});

@@ -429,6 +429,27 @@ def test_bits_do_not_depend_on_the_batch_above_512_rows(dtype):
             assert bits_equal(g[:32], w), f"batch {B}, call {k}"
 
 
+@pytest.mark.parametrize("dim", [192, 512])
+def test_rows_with_a_large_mean_are_normalised_alike(dim):
+    """The input bias raised by 30 gives rows whose mean is tens of their
+    deviations; rounding the mean (2^-24 of it, the same for the whole row) then
+    is most of the error.  A many-row call (1,664 rows) rounds it as often as a
+    few-row one (208 rows), so their errors against 64 bits agree: one rounding
+    more would be sqrt(2) of that part (measured: 1.02, with one more 1.16 to 1.24)."""
+    a = dict(TINY, dim=dim, heads=dim // 64, mlp=512, n_mel=24, depth=1, n_steps=1, f_prompt=9, f_retained=8,
+             f_chunk=8, f_call=13)
+    blob = synth.make_flow_weights(a, 21)
+    synth.split_flow_weights(a, blob)["in.b"][:] += 30.0   # (views of the blob)
+    rel = []
+    for B in (8, 64):
+        dec, outs, mu, prompts = _run_gpu(a, "f32", blob, B, 9, [13])
+        dec.close()
+        ref = np.stack([_run_oracle(a, "f32", blob, b, prompts[b], mu[b], [13])[1][0] for b in range(8)])
+        rel.append(err_stats(outs[0][:8], ref)[1])
+    say(f"  few rows {rel[0]:.3e}, many {rel[1]:.3e}")
+    assert rel[1] <= 1.1 * rel[0]
+
+
 def test_real_shape_batch20_every_tile_size():
     """20 paper-shaped streams in bf16: 2,240 rows per call, so the MLP-up GEMM
     takes 128 x 128 tiles, the input, QKV, attention-output and MLP-down GEMMs
