@@ -847,10 +847,15 @@ __device__ __forceinline__ void conv_body(const ConvGroup& g)
     }
 
     if constexpr (X3) {
+        // an infinite operand has made the sum of the leading products what fp32
+        // MFMA gives; its products with lower planes, zeros or of the other sign,
+        // are NaNs and stay out
 #pragma unroll
         for (int i = 0; i < MB; i++)
 #pragma unroll
-            for (int j = 0; j < NB; j++) acc[i][j] += low[i][j];
+            for (int j = 0; j < NB; j++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc[i][j][e] += fabsf(acc[i][j][e]) < INFINITY ? low[i][j][e] : 0.f;
     }
 
     // ---- epilogue: bias, residual, branch mean, LeakyReLU, store through the rings

@@ -415,3 +415,37 @@ def test_f32_planes_edges_match_oracle(C, rb_kernel, dil, planes):
             one = pcm
         elif B == 7:
             assert bits_equal(pcm[:1], one)
+
+
+@pytest.mark.parametrize("C,B", [(64, 1), (128, 1), (64, 9)])   # two, four and no K partitions
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_f32_planes_keep_infinities(C, B, sign):
+    """An infinite bias or weight in an fp32 resblock gives the infinity that the
+    sum has, as the definition does: where all its terms have one sign there is
+    no NaN, whatever the lower planes of the other operand are."""
+    arch = dict(TINY, n_pre=1, up_rate=[2, 2], channels=[64, C, 64], rb_kernel=[3], dil=[1, 1])
+    blob = synth.make_weights(arch, 4)
+    w = synth.split_weights(arch, blob)             # views of the blob
+    w["s0.rb0.d0.b1"][5] = np.inf                   # h's channel 5 is infinite on every frame
+    w["s0.rb0.d0.W2"][:, 5] = sign * np.abs(w["s0.rb0.d0.W2"][:, 5])
+    w["s0.rb0.d0.W2"][0, 5] = 2.0 * sign            # a weight whose lower planes are zero
+    w["s0.rb0.d0.W1"][3, 2, -1] = sign * np.inf     # h's channel 3: the sign of channel 2 of the same frame
+    w["s0.rb0.d0.W2"][:, 3] = 0.0                   # (0 times an infinity: below, without it)
+    ids = synth.make_tokens(arch, B, 8)
+
+    def taps():
+        dec = dc.Decoder(arch, "f32", blob, batch=B, chunk_tokens=8)
+        assert any(l["kernel"].startswith("dc::xconv_kernel") for l in dec.layers())
+        dec.decode(ids)
+        dec.sync()
+        out = {n: dec.tap(n, B - 1, 0, 16) for n in ("s0.y", "s0.rb0.h0", "s0.rb0.z0")}
+        dec.close()
+        return out
+
+    t = taps()
+    assert np.isposinf(t["s0.rb0.h0"][:, 5]).all()
+    assert np.array_equal(t["s0.rb0.h0"][:, 3], sign * np.inf * t["s0.y"][:, 2])
+    assert np.isnan(t["s0.rb0.z0"]).all()           # h's infinite channel 3 times a zero weight
+    w["s0.rb0.d0.W1"][3, 2, -1] = 0.5
+    t = taps()
+    assert np.isfinite(t["s0.rb0.h0"][:, 3]).all() and np.array_equal(t["s0.rb0.z0"], np.full_like(t["s0.rb0.z0"], sign * np.inf))
