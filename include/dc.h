@@ -210,17 +210,23 @@ dc_status dc_decode_chunk_f0(dc_state* s, const int32_t* tokens, const float* f0
  * DC_HOST_PTRS state).  It comes after every earlier call of this state, and
  * every later call of any kind after it.  A caller whose inputs and outputs
  * live on its own stream so needs no event and no wait on it.  Other work that
- * the caller itself puts on the state's stream comes after this call only once
- * dc_settle (or any call that uses that stream) has been called.  The device
- * of hip_stream has to be the state's.  Not while hip_stream is being captured
- * (the state's own stream would join the capture).  Errors as
- * dc_decode_chunk_f0.
+ * the caller itself puts on the state's stream is ordered with such calls only
+ * by dc_settle.  The device of hip_stream has to be the state's.  DC_ESTATE,
+ * with nothing launched, while hip_stream is being captured, or the state's own
+ * stream is with work to wait for (an event would pull the one into the other's
+ * capture).  Errors otherwise as dc_decode_chunk_f0.
  */
 dc_status dc_decode_chunk_on(dc_state* s, void* hip_stream, const int32_t* tokens, const float* f0, int32_t n,
                              float* audio_out);
 
-/* Order the state's own stream after every call made with dc_decode_chunk_on
- * (asynchronous). */
+/* Order the state's own stream after every call made with dc_decode_chunk_on,
+ * and the next such call after what the state's own stream then holds and is
+ * given until that call (asynchronous).  Every call on the state's own stream
+ * does so itself, except while that stream is being captured: a captured stream
+ * cannot wait for a call outside the capture, so dc_settle comes before the
+ * capture begins.  In it, as long as such a wait is due, dc_settle and every
+ * call on that stream return DC_ESTATE and launch nothing, and the capture
+ * stays valid. */
 dc_status dc_settle(dc_state* s);
 
 /*

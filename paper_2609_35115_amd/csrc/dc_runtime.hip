@@ -168,6 +168,7 @@ static dc_status fail(dc_state* s, dc_status code, const std::string& why)
 static dc_status device_fail(dc_state* s, hipError_t e, const char* where)
 {
     s->poisoned = true;
+    (void)hipGetLastError();   // reported here, not again by the check of a later launch
     return fail(s, DC_EDEVICE, std::string(where) + ": " + hipGetErrorString(e));
 }
 
@@ -1023,30 +1024,42 @@ static hipError_t enqueue_step(dc_state* s, int n, hipStream_t st, double* ptab 
     return e;
 }
 
-// The state's own stream, for work: after the calls made on others.
-static hipStream_t home(dc_state* s)
+static bool capturing(hipStream_t st)
 {
-    s->home_work = true;
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &c) == hipSuccess && c != hipStreamCaptureStatusNone;
+}
+
+// Makes the state's own stream ready for work: after the calls made on others.
+// A wait that cannot be enqueued stays due; under capture it is not tried, as
+// it would end the capture (the event was recorded outside it).
+static dc_status home(dc_state* s)
+{
     if (s->on_pending) {
+        if (capturing(s->stream))
+            return fail(s, DC_ESTATE, "the state's stream is being captured before it waited for dc_decode_chunk_on: "
+                                      "call dc_settle first");
+        const hipError_t e = hipStreamWaitEvent(s->stream, s->on_ev, 0);
+        if (e != hipSuccess) return device_fail(s, e, "stream hand-over");
         s->on_pending = false;
-        if (hipStreamWaitEvent(s->stream, s->on_ev, 0) != hipSuccess) (void)hipEventSynchronize(s->on_ev);
     }
-    return s->stream;
+    s->home_work = true;
+    return DC_OK;
 }
 
 static hipError_t zero_state(dc_state* s)
 {
-    hipError_t e = hipMemsetAsync(s->arena + s->ring_begin, 0, s->ring_end - s->ring_begin, home(s));
+    hipError_t e = hipMemsetAsync(s->arena + s->ring_begin, 0, s->ring_end - s->ring_begin, s->stream);
     if (e != hipSuccess) return e;
-    e = hipMemsetAsync(s->clock, 0, sizeof(int64_t), home(s));
+    e = hipMemsetAsync(s->clock, 0, sizeof(int64_t), s->stream);
     if (e != hipSuccess) return e;
-    e = hipMemsetAsync(s->start, 0, (size_t)s->cfg.batch * sizeof(int64_t), home(s));
+    e = hipMemsetAsync(s->start, 0, (size_t)s->cfg.batch * sizeof(int64_t), s->stream);
     if (e != hipSuccess) return e;
-    e = launch_init_keys(s->keys, s->cfg.batch, home(s));
+    e = launch_init_keys(s->keys, s->cfg.batch, s->stream);
     if (e != hipSuccess) return e;
-    e = hipMemsetAsync(s->arrivals, 0, sizeof(unsigned), home(s));
+    e = hipMemsetAsync(s->arrivals, 0, sizeof(unsigned), s->stream);
     if (e != hipSuccess) return e;
-    return hipMemsetAsync(s->err, 0, sizeof(int), home(s));
+    return hipMemsetAsync(s->err, 0, sizeof(int), s->stream);
 }
 
 // ------------------------------------------------------------------ the ABI
@@ -1325,15 +1338,16 @@ static hipError_t leave_on(dc_state* s, hipStream_t st)
     s->on_stream = st;
     s->on_any = s->on_pending = true;
     s->home_work = false;
-    return hipEventRecord(s->on_ev, st);
+    const hipError_t e = hipEventRecord(s->on_ev, st);
+    if (e != hipSuccess) {   // nothing to wait for later: wait now
+        s->on_any = s->on_pending = false;
+        (void)hipStreamSynchronize(st);
+    }
+    return e;
 }
 
-// One call: admission, staging of tokens (and f0), replay or direct launch,
-// staging of the PCM.  f0 is non-null exactly for a decoder with a source.
-// static_ptab non-null: dc_decode_chunk_f0_static (direct launches whose phase
-// table is the device's static scratch; never a graph replay).
-static dc_status decode_call(dc_state* s, const int32_t* tokens, const float* f0, int32_t n, float* audio_out,
-                             hipStream_t st, double* static_ptab = nullptr)
+// Admission of one call (refused ones launch nothing).
+static dc_status admit(dc_state* s, const int32_t* tokens, const float* f0, int32_t n, const float* audio_out)
 {
     if (s->poisoned) return fail(s, DC_ESTATE, "state is poisoned; call dc_reset");
     const dc_cfg& c = s->cfg;
@@ -1349,16 +1363,27 @@ static dc_status decode_call(dc_state* s, const int32_t* tokens, const float* f0
         s->st.rejected++;
         return fail(s, DC_ERANGE, "n exceeds max_tokens");
     }
-    const bool host = (c.flags & DC_HOST_PTRS) != 0;
-    const size_t tok_bytes = (size_t)c.batch * n * sizeof(int32_t);
-    const size_t pcm_bytes = (size_t)c.batch * n * s->spt * sizeof(float);
-    if (host) {
+    if (c.flags & DC_HOST_PTRS) {
         for (size_t i = 0; i < (size_t)c.batch * n; i++)
             if (tokens[i] < 0 || tokens[i] >= c.vocab) {
                 s->st.rejected++;
                 return fail(s, DC_ERANGE, "token id outside [0, vocab)");
             }
     }
+    return DC_OK;
+}
+
+// One admitted call on stream st: staging of tokens (and f0), replay or direct
+// launch, staging of the PCM.  f0 is non-null exactly for a decoder with a
+// source.  static_ptab non-null: dc_decode_chunk_f0_static (direct launches
+// whose phase table is the device's static scratch; never a graph replay).
+static dc_status run_call(dc_state* s, const int32_t* tokens, const float* f0, int32_t n, float* audio_out,
+                          hipStream_t st, double* static_ptab = nullptr)
+{
+    const dc_cfg& c = s->cfg;
+    const bool host = (c.flags & DC_HOST_PTRS) != 0;
+    const size_t tok_bytes = (size_t)c.batch * n * sizeof(int32_t);
+    const size_t pcm_bytes = (size_t)c.batch * n * s->spt * sizeof(float);
     hipError_t e = hipSuccess;
     if (tokens != s->tok) {
         e = host ? hipMemcpyAsync(s->tok, tokens, tok_bytes, hipMemcpyHostToDevice, st)
@@ -1404,6 +1429,20 @@ static dc_status decode_call(dc_state* s, const int32_t* tokens, const float* f0
     return DC_OK;
 }
 
+// A call on the state's own stream.
+static dc_status home_call(dc_state* s, const int32_t* tokens, const float* f0, int32_t n, float* audio_out,
+                           double* static_ptab = nullptr)
+{
+    dc_status status = admit(s, tokens, f0, n, audio_out);
+    if (status != DC_OK) return status;
+    status = home(s);
+    if (status != DC_OK) {
+        s->st.rejected++;
+        return status;
+    }
+    return run_call(s, tokens, f0, n, audio_out, s->stream, static_ptab);
+}
+
 dc_status dc_decode_chunk(dc_state* s, const int32_t* tokens, int32_t n, float* audio_out)
 {
     if (!s) return DC_EINVAL;
@@ -1411,7 +1450,7 @@ dc_status dc_decode_chunk(dc_state* s, const int32_t* tokens, int32_t n, float* 
         s->st.rejected++;
         return fail(s, DC_EINVAL, "this decoder has a harmonic source: call dc_decode_chunk_f0");
     }
-    return decode_call(s, tokens, nullptr, n, audio_out, home(s));
+    return home_call(s, tokens, nullptr, n, audio_out);
 }
 
 dc_status dc_decode_chunk_f0(dc_state* s, const int32_t* tokens, const float* f0, int32_t n, float* audio_out)
@@ -1421,7 +1460,7 @@ dc_status dc_decode_chunk_f0(dc_state* s, const int32_t* tokens, const float* f0
         s->st.rejected++;
         return fail(s, DC_EINVAL, "this decoder has no harmonic source: call dc_decode_chunk");
     }
-    return decode_call(s, tokens, f0, n, audio_out, home(s));
+    return home_call(s, tokens, f0, n, audio_out);
 }
 
 dc_status dc_decode_chunk_on(dc_state* s, void* hip_stream, const int32_t* tokens, const float* f0, int32_t n,
@@ -1437,10 +1476,18 @@ dc_status dc_decode_chunk_on(dc_state* s, void* hip_stream, const int32_t* token
         return fail(s, DC_EINVAL, why);
     }
     const hipStream_t st = (hipStream_t)hip_stream;
-    if (st == s->stream) return decode_call(s, tokens, f0, n, audio_out, home(s));
+    if (st == s->stream) return home_call(s, tokens, f0, n, audio_out);
+    dc_status status = admit(s, tokens, f0, n, audio_out);
+    if (status != DC_OK) return status;
+    // an event between a captured and an uncaptured stream would pull the one
+    // into the other's capture
+    if (capturing(st) || (s->home_work && capturing(s->stream))) {
+        s->st.rejected++;
+        return fail(s, DC_ESTATE, "the call's stream, or the state's with work to wait for, is being captured");
+    }
     hipError_t e = enter_on(s, st);
     if (e != hipSuccess) return device_fail(s, e, "stream hand-over");
-    const dc_status status = decode_call(s, tokens, f0, n, audio_out, st);
+    status = run_call(s, tokens, f0, n, audio_out, st);
     e = leave_on(s, st);   // also after a failure: what was launched comes before the state's later work
     if (e != hipSuccess) return device_fail(s, e, "stream hand-over");
     return status;
@@ -1500,20 +1547,20 @@ dc_status dc_decode_chunk_f0_static(dc_state* s, const int32_t* tokens, const fl
         }
     }
     if (!s->static_ptab) return fail(s, DC_EDEVICE, "static scratch address was not resolved at dc_init");
-    return decode_call(s, tokens, f0, n, audio_out, home(s), s->static_ptab);
+    return home_call(s, tokens, f0, n, audio_out, s->static_ptab);
 }
 
 dc_status dc_settle(dc_state* s)
 {
-    if (!s) return DC_EINVAL;
-    (void)home(s);
-    return DC_OK;
+    return s ? home(s) : DC_EINVAL;
 }
 
 dc_status dc_sync(dc_state* s)
 {
     if (!s) return DC_EINVAL;
-    hipError_t e = hipStreamSynchronize(home(s));
+    const dc_status ready = home(s);
+    if (ready != DC_OK) return ready;
+    hipError_t e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return device_fail(s, e, "hipStreamSynchronize");
     s->home_work = false;
     int flag = 0;
@@ -1531,8 +1578,10 @@ dc_status dc_sync(dc_state* s)
 dc_status dc_reset(dc_state* s)
 {
     if (!s) return DC_EINVAL;
+    const dc_status ready = home(s);
+    if (ready != DC_OK) return ready;
     hipError_t e = zero_state(s);
-    if (e == hipSuccess) e = hipStreamSynchronize(home(s));
+    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return device_fail(s, e, "dc_reset");
     s->poisoned = false;
     s->clock_host = 0;
@@ -1543,14 +1592,16 @@ dc_status dc_reset_stream(dc_state* s, int32_t b)
 {
     if (!s) return DC_EINVAL;
     if (b < 0 || b >= s->cfg.batch) return fail(s, DC_EINVAL, "stream index out of range");
+    const dc_status ready = home(s);
+    if (ready != DC_OK) return ready;
     for (const Ring& r : s->rings) {
         const size_t es = elem_bytes(r.elem);
         const size_t per = (size_t)r.R * r.C * es;
-        hipError_t e = hipMemsetAsync((char*)r.ptr + (size_t)b * per, 0, per, home(s));
+        hipError_t e = hipMemsetAsync((char*)r.ptr + (size_t)b * per, 0, per, s->stream);
         if (e != hipSuccess) return device_fail(s, e, "dc_reset_stream");
     }
     // fused pairs recompute h of the left context: frames before this point are zeros
-    hipError_t e = launch_mark_start(s->start, s->keys, b, s->clock, 0, (uint64_t)b, home(s));
+    hipError_t e = launch_mark_start(s->start, s->keys, b, s->clock, 0, (uint64_t)b, s->stream);
     if (e != hipSuccess) return device_fail(s, e, "dc_reset_stream");
     return DC_OK;
 }
@@ -1647,7 +1698,9 @@ dc_status dc_carry_export(dc_state* s, int32_t b, void* host_out, size_t bytes)
     if (b < 0 || b >= s->cfg.batch || !host_out) return fail(s, DC_EINVAL, "bad stream index or buffer");
     if (bytes != snapshot_bytes(s)) return fail(s, DC_EINVAL, "buffer size differs from dc_carry_bytes");
     if (s->poisoned) return fail(s, DC_ESTATE, "state is poisoned; call dc_reset");
-    hipError_t e = hipStreamSynchronize(home(s));
+    const dc_status ready = home(s);
+    if (ready != DC_OK) return ready;
+    hipError_t e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return device_fail(s, e, "dc_carry_export");
     int64_t start = 0;
     uint64_t key = 0;
@@ -1693,7 +1746,9 @@ dc_status dc_carry_import(dc_state* s, int32_t b, const void* host_in, size_t by
         return fail(s, DC_EINVAL, "snapshot of a different architecture, dtype or ring layout");
     if (hd.position < 0) return fail(s, DC_EINVAL, "bad snapshot position");
     if (s->poisoned) return fail(s, DC_ESTATE, "state is poisoned; call dc_reset");
-    hipError_t e = hipStreamSynchronize(home(s));
+    const dc_status ready = home(s);
+    if (ready != DC_OK) return ready;
+    hipError_t e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return device_fail(s, e, "dc_carry_import");
     // the stream's rings start clean, then take the carried frames
     for (const Ring& r : s->rings) {
@@ -1720,8 +1775,8 @@ dc_status dc_carry_import(dc_state* s, int32_t b, const void* host_in, size_t by
         if (e != hipSuccess) return device_fail(s, e, "dc_carry_import");
     }
     // the stream started `position` tokens before this state's next call
-    e = launch_mark_start(s->start, s->keys, b, s->clock, hd.position, hd.key, home(s));
-    if (e == hipSuccess) e = hipStreamSynchronize(home(s));
+    e = launch_mark_start(s->start, s->keys, b, s->clock, hd.position, hd.key, s->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return device_fail(s, e, "dc_carry_import");
     return DC_OK;
 }
@@ -1752,7 +1807,9 @@ dc_status dc_tap_read(dc_state* s, int32_t tap, int32_t b, int64_t frame0, int32
     if (channels) *channels = r.C;
     const int64_t end = s->clock_host * s->fpt[r.level];
     if (frame0 < end - r.R || frame0 + nframes > end) return fail(s, DC_ERANGE, "frames not held by the ring");
-    hipError_t e = hipStreamSynchronize(home(s));
+    const dc_status ready = home(s);
+    if (ready != DC_OK) return ready;
+    hipError_t e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return device_fail(s, e, "dc_tap_read");
     const size_t es = elem_bytes(r.elem);
     std::vector<char> row((size_t)r.C * es);
@@ -1865,16 +1922,18 @@ dc_status dc_time_layers(dc_state* s, int32_t reps, double* us_per_launch)
 {
     if (!s || !us_per_launch || reps < 1) return fail(s, DC_EINVAL, "bad dc_time_layers arguments");
     if (s->poisoned) return fail(s, DC_ESTATE, "state is poisoned; call dc_reset");
+    const dc_status ready = home(s);
+    if (ready != DC_OK) return ready;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     const int nl = layer_count(s);
     for (int i = 0; i < nl && e == hipSuccess; i++) {   // re-runs leave the clock where it is
-        e = launch_layer(s, i, s->cfg.chunk_tokens, home(s), nullptr, true);   // warm
-        if (e == hipSuccess) e = hipEventRecord(e0, home(s));
+        e = launch_layer(s, i, s->cfg.chunk_tokens, s->stream, nullptr, true);   // warm
+        if (e == hipSuccess) e = hipEventRecord(e0, s->stream);
         for (int r = 0; r < reps && e == hipSuccess; r++)
-            e = launch_layer(s, i, s->cfg.chunk_tokens, home(s), nullptr, true);
-        if (e == hipSuccess) e = hipEventRecord(e1, home(s));
+            e = launch_layer(s, i, s->cfg.chunk_tokens, s->stream, nullptr, true);
+        if (e == hipSuccess) e = hipEventRecord(e1, s->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
