@@ -109,9 +109,8 @@ struct dc_state {
     hipStream_t side = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
     int src_join = -1;          // index of the launch that reads the source ring
-    // dc_decode_chunk_on: the stream and the end of its last call, whether the
-    // state's own stream has yet to wait for it, and whether it has had work since
-    hipStream_t on_stream = nullptr;
+    // dc_decode_chunk_on: the end of its last call, whether there was one, whether
+    // the state's own stream has yet to wait for it, and whether it has had work since
     hipEvent_t on_ev = nullptr, home_ev = nullptr;
     bool on_any = false, on_pending = false, home_work = false;
     char* arena = nullptr;
@@ -1329,13 +1328,15 @@ static hipError_t enter_on(dc_state* s, hipStream_t st)
         e = hipEventRecord(s->home_ev, s->stream);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, s->home_ev, 0);
     }
-    if (e == hipSuccess && s->on_any && s->on_stream != st) e = hipStreamWaitEvent(st, s->on_ev, 0);
+    // (also where st is the last call's handle: that can name another stream by now,
+    // a thread's own one or a new one at a destroyed one's address; the runtime
+    // knows, and a wait for the stream's own event costs nothing measurable)
+    if (e == hipSuccess && s->on_any) e = hipStreamWaitEvent(st, s->on_ev, 0);
     return e;
 }
 
 static hipError_t leave_on(dc_state* s, hipStream_t st)
 {
-    s->on_stream = st;
     s->on_any = s->on_pending = true;
     s->home_work = false;
     const hipError_t e = hipEventRecord(s->on_ev, st);

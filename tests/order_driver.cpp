@@ -375,11 +375,33 @@ static void failing_wait()
     }
 }
 
+// One handle value, several streams: the per-thread stream of two threads, and a
+// destroyed stream's handle handed out again.
+static void same_handle()
+{
+    Fixture f;
+    for (int i = 0; i < 4; i++) {
+        if (i % 2) std::thread([&] { expect(f.on(hipStreamPerThread) == DC_OK, "a call on a thread's stream"); }).join();
+        else expect(f.on(hipStreamPerThread) == DC_OK, "a call on this thread's stream");
+    }
+    expect(g_unordered == 0, "the per-thread streams are in order");
+    hipStream_t old = nullptr;
+    for (int i = 0; i < 3; i++) {
+        hipStream_t st;
+        (void)hipStreamCreateWithFlags(&st, 0);
+        expect(!old || st == old, "(the handle is used again)");
+        expect(f.on(st) == DC_OK, "a call on a new stream");
+        (void)hipStreamDestroy(old = st);
+    }
+    expect(g_unordered == 0, "the streams of one handle are in order");
+}
+
 int main(int argc, char** argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
     const std::map<std::string, void (*)()> all = {
-        {"several_streams", several_streams}, {"settle", settle}, {"capture", capture}, {"failing_wait", failing_wait}};
+        {"several_streams", several_streams}, {"settle", settle}, {"capture", capture}, {"failing_wait", failing_wait},
+        {"same_handle", same_handle}};
     if (all.count(which)) all.at(which)();
     else expect(false, "unknown scenario");
     std::printf("failures %d\n", g_failures);
