@@ -40,9 +40,11 @@ static inline hipError_t stage_async(void* dst, const void* src, size_t bytes, i
     const bool wide = (((uintptr_t)dst | (uintptr_t)src | bytes) & 15) == 0;
     const int64_t n = (int64_t)(bytes / (wide ? 16 : 4));
     const unsigned blocks = (unsigned)(n < 256 * 2048 ? (n + 255) / 256 : 2048);
-    if (wide) hipLaunchKernelGGL((stage_kernel<uint4>), dim3(blocks), dim3(256), 0, st, (uint4*)dst, (const uint4*)src, n);
-    else hipLaunchKernelGGL((stage_kernel<uint32_t>), dim3(blocks), dim3(256), 0, st, (uint32_t*)dst, (const uint32_t*)src, n);
-    return hipGetLastError();
+    // (hipLaunchKernel for its own status: hipGetLastError would report, and take,
+    // an error of the caller's that has nothing to do with the copy)
+    void* args[] = {&dst, &src, (void*)&n};
+    return hipLaunchKernel(wide ? (const void*)&stage_kernel<uint4> : (const void*)&stage_kernel<uint32_t>, dim3(blocks),
+                           dim3(256), args, 0, st);
 }
 
 }  // namespace dc

@@ -396,12 +396,24 @@ static void same_handle()
     expect(g_unordered == 0, "the streams of one handle are in order");
 }
 
+// An error of the caller's own is neither the call's nor taken from the caller.
+static void callers_error()
+{
+    Fixture f;
+    for (int i = 0; i < 4; i++) {
+        t_err = hipErrorOutOfMemory;
+        expect((i % 2 ? f.home() : f.on(f.a)) == DC_OK, "a replay after a failed call of the caller's");
+        expect(hipGetLastError() == hipErrorOutOfMemory, "whose error is still there");
+    }
+    expect(dc_sync(f.s) == DC_OK, "a sound state");
+}
+
 int main(int argc, char** argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
     const std::map<std::string, void (*)()> all = {
         {"several_streams", several_streams}, {"settle", settle}, {"capture", capture}, {"failing_wait", failing_wait},
-        {"same_handle", same_handle}};
+        {"same_handle", same_handle}, {"callers_error", callers_error}};
     if (all.count(which)) all.at(which)();
     else expect(false, "unknown scenario");
     std::printf("failures %d\n", g_failures);

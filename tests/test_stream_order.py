@@ -36,7 +36,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["several_streams", "settle", "capture", "failing_wait", "same_handle"])
+@pytest.mark.parametrize("scenario", ["several_streams", "settle", "capture", "failing_wait", "same_handle",
+                                      "callers_error"])
 def test_device_work_is_in_order(driver, scenario):
     r = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "failures 0" in r.stdout, r.stdout + r.stderr
