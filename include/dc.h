@@ -211,7 +211,9 @@ dc_status dc_decode_chunk_f0(dc_state* s, const int32_t* tokens, const float* f0
  * every later call of any kind after it.  A caller whose inputs and outputs
  * live on its own stream so needs no event and no wait on it.  Other work that
  * the caller itself puts on the state's stream is ordered with such calls only
- * by dc_settle.  The device of hip_stream has to be the state's.  DC_ESTATE,
+ * by dc_settle.  The device of hip_stream has to be the state's; hip_stream may
+ * be destroyed, and its thread end, once the call has returned (a call on
+ * hipStreamPerThread is handed over to the state's own stream and back).  DC_ESTATE,
  * with nothing launched, while hip_stream is being captured, or the state's own
  * stream is with work to wait for (an event would pull the one into the other's
  * capture).  Errors otherwise as dc_decode_chunk_f0.

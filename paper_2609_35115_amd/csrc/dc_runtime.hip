@@ -1316,21 +1316,24 @@ dc_status dc_init(const void* weights_blob, size_t blob_bytes, const dc_cfg* cfg
 // own stream waits for it when it is next used (settle): handing every call
 // over to it and back cost 45 us between the two waits, and a wait on it alone
 // after every call still 26 us, for a tiny decoder's 89 us.
+static hipError_t on_events(dc_state* s)
+{
+    if (s->on_ev) return hipSuccess;
+    s->home_work = true;
+    const hipError_t e = hipEventCreateWithFlags(&s->home_ev, hipEventDisableTiming);
+    return e == hipSuccess ? hipEventCreateWithFlags(&s->on_ev, hipEventDisableTiming) : e;
+}
+
 static hipError_t enter_on(dc_state* s, hipStream_t st)
 {
-    hipError_t e = hipSuccess;
-    if (!s->on_ev) {
-        e = hipEventCreateWithFlags(&s->on_ev, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&s->home_ev, hipEventDisableTiming);
-        s->home_work = true;
-    }
+    hipError_t e = on_events(s);
     if (e == hipSuccess && s->home_work) {
         e = hipEventRecord(s->home_ev, s->stream);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, s->home_ev, 0);
     }
     // (also where st is the last call's handle: that can name another stream by now,
-    // a thread's own one or a new one at a destroyed one's address; the runtime
-    // knows, and a wait for the stream's own event costs nothing measurable)
+    // a new one at a destroyed one's address; the runtime knows, and a wait for the
+    // stream's own event costs nothing measurable)
     if (e == hipSuccess && s->on_any) e = hipStreamWaitEvent(st, s->on_ev, 0);
     return e;
 }
@@ -1345,6 +1348,18 @@ static hipError_t leave_on(dc_state* s, hipStream_t st)
         (void)hipStreamSynchronize(st);
     }
     return e;
+}
+
+// The calling thread's own stream and the state's, one after the other: the
+// first waits for what the second holds so far.  A call on hipStreamPerThread
+// runs on the state's own stream between two of these (45 us more for a tiny
+// decoder), as the thread may end after it: while it does, the runtime takes its
+// stream's events for done, and a later call's wait would be none.
+static hipError_t chain(dc_state* s, hipStream_t first, hipStream_t second)
+{
+    hipError_t e = on_events(s);
+    if (e == hipSuccess) e = hipEventRecord(s->home_ev, second);
+    return e == hipSuccess ? hipStreamWaitEvent(first, s->home_ev, 0) : e;
 }
 
 // Admission of one call (refused ones launch nothing).
@@ -1482,9 +1497,19 @@ dc_status dc_decode_chunk_on(dc_state* s, void* hip_stream, const int32_t* token
     if (status != DC_OK) return status;
     // an event between a captured and an uncaptured stream would pull the one
     // into the other's capture
-    if (capturing(st) || (s->home_work && capturing(s->stream))) {
+    if (capturing(st) || ((s->home_work || st == hipStreamPerThread) && capturing(s->stream))) {
         s->st.rejected++;
         return fail(s, DC_ESTATE, "the call's stream, or the state's with work to wait for, is being captured");
+    }
+    if (st == hipStreamPerThread) {
+        status = home(s);
+        if (status != DC_OK) return status;
+        hipError_t e = chain(s, s->stream, st);
+        if (e == hipSuccess) {
+            status = run_call(s, tokens, f0, n, audio_out, s->stream);
+            e = chain(s, st, s->stream);
+        }
+        return e == hipSuccess ? status : device_fail(s, e, "stream hand-over");
     }
     hipError_t e = enter_on(s, st);
     if (e != hipSuccess) return device_fail(s, e, "stream hand-over");

@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 #include <thread>
 #include <vector>
@@ -42,11 +43,17 @@ struct Clock {
         return true;
     }
 };
+static std::set<int> g_ended;   // queues of ended threads
 struct Queue {   // what a stream handle names
     int id;
     Clock c;
     bool cap = false, bad = false;   // being captured; that capture is invalid
+    bool of_thread = false;
     Queue() : id(next()++) {}
+    ~Queue()
+    {
+        if (of_thread) g_ended.insert(id);
+    }
     static int& next()
     {
         static int n = 0;
@@ -58,6 +65,7 @@ struct ihipStream_t {
 };
 struct ihipEvent_t {
     Clock c;
+    int queue = -1;
     bool cap = false;
 };
 struct ihipGraph {
@@ -83,6 +91,7 @@ static hipError_t ret(hipError_t e)
 static Queue& queue(hipStream_t s)
 {
     static thread_local Queue per_thread;
+    per_thread.of_thread = true;
     if (!s) return g_default;
     if (s == hipStreamPerThread) return per_thread;
     return *s->q;
@@ -210,6 +219,7 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms =
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 {
     e->cap = queue(s).cap;
+    e->queue = queue(s).id;
     e->c = queue(s).c;
     e->c.merge(g_host);
     return hipSuccess;
@@ -231,6 +241,7 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
         q.cap = true;
         g_captured.push_back(&q);
     }
+    if (g_ended.count(e->queue)) return hipSuccess;   // taken for done, though the thread may still be ending
     q.c.merge(e->c);
     return hipSuccess;
 }
@@ -384,6 +395,10 @@ static void same_handle()
         if (i % 2) std::thread([&] { expect(f.on(hipStreamPerThread) == DC_OK, "a call on a thread's stream"); }).join();
         else expect(f.on(hipStreamPerThread) == DC_OK, "a call on this thread's stream");
     }
+    std::thread([&] { expect(f.on(hipStreamPerThread) == DC_OK, "a call on another thread's stream"); }).join();
+    expect(f.home() == DC_OK, "a call on the state's stream");
+    std::thread([&] { expect(f.on(hipStreamPerThread) == DC_OK, "a call on another thread's stream"); }).join();
+    expect(f.on(f.a) == DC_OK, "a call on a stream");
     expect(g_unordered == 0, "the per-thread streams are in order");
     hipStream_t old = nullptr;
     for (int i = 0; i < 3; i++) {
