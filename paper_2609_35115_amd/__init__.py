@@ -384,10 +384,13 @@ def check_decode_args(tokens, f0, batch: int, max_tokens: int, fpt: int, has_sou
 
 
 class Decoder:
-    """One dc_state on the current GPU, with torch-ROCm tensors for device memory.
-    Decodes are ordered on the caller's current stream, as torch operations are;
-    the C calls on the handle run on the state's own stream (`stream`, a dedicated
-    torch stream), each after every decode before it."""
+    """One dc_state on the current GPU, with torch-ROCm tensors for device memory
+    and a dedicated torch stream (`stream`).  Decodes are ordered on the caller's
+    current stream, as torch operations are, and in any case after every earlier
+    call; the C calls on the handle run on `stream`, each after every decode
+    before it.  Once a program has asked for `stream`, every decode is ordered on
+    it too: after the work that the program has put there, and before what it puts
+    there next."""
 
     def __init__(self, arch: dict, dtype: str, blob: np.ndarray, batch: int, chunk_tokens: int,
                  max_tokens: int | None = None, flags: int = 0, tile_variant: int = 0, rng_seed: int = 0):
@@ -396,6 +399,7 @@ class Decoder:
         self.arch, self.dtype, self.batch = arch, dtype, batch
         self.host = bool(flags & DC_HOST_PTRS)
         self._stream = torch.cuda.Stream()
+        self._shared = False   # the program may hold `stream`
         self.device = torch.cuda.current_device()
         self.cfg = make_cfg(arch, dtype, batch, chunk_tokens, max_tokens, flags, tile_variant,
                             self._stream.cuda_stream, rng_seed)
@@ -407,10 +411,15 @@ class Decoder:
 
     @property
     def stream(self):
-        """The state's own stream, ordered after every decode so far."""
-        if self.h is not None:
-            dc_settle(self.h)
+        """The state's own stream, ordered after every decode so far.  From now on
+        every decode settles the order with it (26 us a call of a tiny decoder)."""
+        self._shared = True
+        self._settle()
         return self._stream
+
+    def _settle(self):
+        if self.h is not None:
+            _check(dc_settle(self.h), self.h)
 
     def close(self):
         if self.h is not None:
@@ -456,9 +465,14 @@ class Decoder:
             elif f0 is not None:
                 f0d = f0.contiguous()
             out = torch.empty((self.batch, n * self.spt), dtype=torch.float32, device="cuda")
+            if self._shared:
+                self._settle()   # after what the program has put on `stream`
             st = dc_decode_chunk_on(self.h, torch.cuda.current_stream().cuda_stream, tok, f0d, n, out)
+            if self._shared:
+                self._settle()   # what it puts there next comes after the call
         else:
-            with torch.cuda.stream(self.stream):
+            self._settle()
+            with torch.cuda.stream(self._stream):
                 if isinstance(tokens, np.ndarray):
                     tok = torch.from_numpy(np.ascontiguousarray(tokens, dtype=np.int32)).to("cuda")
                 else:
@@ -470,17 +484,17 @@ class Decoder:
                     else:
                         f0d = f0.contiguous()
                 out = torch.empty((self.batch, n * self.spt), dtype=torch.float32, device="cuda")
-            self.stream.wait_stream(torch.cuda.current_stream())
+            self._stream.wait_stream(torch.cuda.current_stream())
             if self.has_source:
                 call = dc_decode_chunk_f0_static if static_scratch else dc_decode_chunk_f0
                 st = call(self.h, tok, f0d, n, out)
             else:
                 st = dc_decode_chunk(self.h, tok, n, out)
-            tok.record_stream(self.stream)
+            tok.record_stream(self._stream)
             if f0d is not None:
-                f0d.record_stream(self.stream)
-            out.record_stream(self.stream)
-            torch.cuda.current_stream().wait_stream(self.stream)
+                f0d.record_stream(self._stream)
+            out.record_stream(self._stream)
+            torch.cuda.current_stream().wait_stream(self._stream)
         if check:
             _check(st, self.h)
         return out

@@ -1,13 +1,18 @@
 """The order of a state's device work over its own and its callers' streams, on
 the CPU: the host code of dc_runtime.hip and the kernels' launch code, linked
 with tests/order_driver.cpp, whose model of the HIP runtime's streams, events
-and captures checks that every operation comes after the one before it."""
+and captures checks that every operation comes after the one before it; and the
+binding's share, the calls that Decoder.decode makes around a decode."""
 from __future__ import annotations
 
 import os
 import subprocess
+from types import SimpleNamespace as NS
 
+import numpy as np
 import pytest
+
+import paper_2609_35115_amd as dc
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2609_35115_amd", "csrc")
@@ -41,3 +46,29 @@ def driver(tmp_path_factory):
 def test_device_work_is_in_order(driver, scenario):
     r = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "failures 0" in r.stdout, r.stdout + r.stderr
+
+
+def test_a_held_stream_is_settled_around_every_decode(monkeypatch):
+    """Once a program has read Decoder.stream, each decode on another stream is
+    ordered with it both ways (what dc_settle does: the `settle` scenario above);
+    before, none is."""
+    calls = []
+    monkeypatch.setattr(dc, "dc_decode_chunk_on", lambda *a: calls.append("decode") or dc.DC_OK)
+    monkeypatch.setattr(dc, "dc_settle", lambda h: calls.append("settle") or dc.DC_OK)
+    monkeypatch.setattr(dc, "dc_free", lambda h: None)
+    dec = dc.Decoder.__new__(dc.Decoder)
+    current = NS(cuda_stream=7)
+    dec.torch = NS(cuda=NS(current_device=lambda: 0, is_current_stream_capturing=lambda: False,
+                           current_stream=lambda: current),
+                   from_numpy=lambda a: NS(to=lambda d: a), empty=lambda *a, **k: object(), float32=None)
+    dec.h, dec.host, dec.device, dec.batch, dec.max_tokens, dec.spt, dec.has_source = 1, False, 0, 1, 8, 4, False
+    dec.arch, dec._stream, dec._shared = {"frames_per_token": 1}, object(), False
+    ids = np.zeros((1, 8), np.int32)
+    dec.decode(ids)
+    assert calls == ["decode"]
+    held = dec.stream
+    assert held is dec._stream and calls == ["decode", "settle"]
+    del calls[:]
+    dec.decode(ids)
+    dec.decode(ids)
+    assert calls == ["settle", "decode", "settle"] * 2
