@@ -1,8 +1,10 @@
 """Decoder.decode runs on the caller's current stream (dc_decode_chunk_on):
-calls from several streams, mixed with C calls on the state's own stream,
-resets and a captured stream, give the bits of the same calls made one after
-the other on the state's stream."""
+calls from several streams and threads, mixed with C calls and resets on the
+state's own stream and work of the caller's there, none of them waited for, give
+the bits of the same calls made one after the other on the state's stream; so
+does a decode captured after an uncaptured one."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -15,64 +17,146 @@ from tests.gpu_common import bits_equal
 pytestmark = pytest.mark.gpu
 
 CASES = [("tiny", synth.TINY_ARCH, "f32", 2, 8), ("tiny source", synth.TINY_NSF_ARCH, "f32", 2, 8),
-         ("tiny bf16 fused batch", synth.TINY_ARCH, "bf16", 8, 5)]
+         ("tiny bf16 fused batch", synth.TINY_ARCH, "bf16", 8, 5),
+         ("real bf16", synth.REAL_ARCH, "bf16", 16, 25)]   # calls ten times longer than their submission
+PER_THREAD = 2   # hipStreamPerThread
 
 
-def _home(dec, tok, f0, n):
-    """One C call on the state's own stream, waited for."""
-    out = torch.empty((dec.batch, n * dec.spt), dtype=torch.float32, device="cuda")
-    torch.cuda.synchronize()
+def _inputs(arch, B, sizes):
+    """Every call's tokens and f0 on the device."""
+    fpt = arch["frames_per_token"]
+    ids = synth.make_tokens(arch, B, sum(sizes))
+    f0 = synth.make_f0(arch, B, sum(sizes)) if "n_harmonics" in arch else None
+    cuda = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    out, at = [], 0
+    for n in sizes:
+        out.append((cuda(ids[:, at:at + n]), None if f0 is None else cuda(f0[:, at * fpt:(at + n) * fpt])))
+        at += n
+    return out
+
+
+def _home(dec, tok, f0, out):
+    """One C call on the state's own stream, not waited for."""
+    n = tok.shape[1]
     st = (dc.dc_decode_chunk_f0(dec.h, tok, f0, n, out) if dec.has_source else dc.dc_decode_chunk(dec.h, tok, n, out))
     assert st == dc.DC_OK
-    dec.sync()
-    return out.cpu().numpy()
+
+
+def _reference(arch, dtype, blob, B, chunk, inputs, resets=()):
+    """The calls one after the other on the state's stream, each waited for."""
+    ref = dc.Decoder(arch, dtype, blob, B, chunk, chunk, rng_seed=7)
+    want = []
+    for i, (tok, f0) in enumerate(inputs):
+        if i in resets:
+            ref.reset_stream(1)
+        out = torch.empty((B, tok.shape[1] * ref.spt), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        _home(ref, tok, f0, out)
+        ref.sync()
+        want.append(out.cpu().numpy())
+    ref.close()
+    return want
 
 
 @pytest.mark.parametrize("name,arch,dtype,B,chunk", CASES, ids=[c[0] for c in CASES])
 def test_calls_from_several_streams_are_in_order(name, arch, dtype, B, chunk):
     blob = synth.make_weights(arch, 0)
-    sizes = [chunk, chunk, 3, chunk, 1, chunk, chunk, 2, chunk]      # replays and direct launches
-    ids = synth.make_tokens(arch, B, sum(sizes))
-    fpt = arch["frames_per_token"]
-    f0 = synth.make_f0(arch, B, sum(sizes)) if "n_harmonics" in arch else None
-    cuda = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
-    ref, dec = (dc.Decoder(arch, dtype, blob, B, chunk, chunk, rng_seed=7) for _ in range(2))
+    sizes = [chunk, chunk, 3, chunk, 1, chunk, chunk, 2, chunk, chunk, chunk, chunk, 3, chunk]   # replays, direct launches
+    inputs, resets = _inputs(arch, B, sizes), (6, 9)
+    want = _reference(arch, dtype, blob, B, chunk, inputs, resets)
+    dec = dc.Decoder(arch, dtype, blob, B, chunk, chunk, rng_seed=7)
+    got = [torch.empty(w.shape, dtype=torch.float32, device="cuda") for w in want]
     side = [torch.cuda.Stream() for _ in range(2)]
-    at, want, got = 0, [], []
-    for i, n in enumerate(sizes):
-        tok, f = cuda(ids[:, at:at + n]), cuda(None if f0 is None else f0[:, at * fpt:(at + n) * fpt])
-        at += n
-        want.append(_home(ref, tok, f, n))
-        torch.cuda.synchronize()
-        if i % 4 == 3:      # a C call on the state's own stream between calls of others, not waited for
-            out = torch.empty((B, n * dec.spt), dtype=torch.float32, device="cuda")
-            torch.cuda.synchronize()
-            st = (dc.dc_decode_chunk_f0(dec.h, tok, f, n, out) if dec.has_source
-                  else dc.dc_decode_chunk(dec.h, tok, n, out))
-            assert st == dc.DC_OK
-            got.append(out)
+
+    def raw(stream, i):
+        tok, f0 = inputs[i]
+        assert dc.dc_decode_chunk_on(dec.h, stream, tok, f0, tok.shape[1], got[i]) == dc.DC_OK
+
+    torch.cuda.synchronize()
+    for i, (tok, f0) in enumerate(inputs):      # nothing is waited for from here
+        if i in resets:
+            dec.reset_stream(1)
+        how = i % 7
+        if how == 3:
+            _home(dec, tok, f0, got[i])
+        elif how == 5:
+            raw(PER_THREAD, i)
+        elif how == 6:
+            t = threading.Thread(target=raw, args=(PER_THREAD, i))
+            t.start()
+            t.join()
         else:
-            with torch.cuda.stream([torch.cuda.default_stream(), side[0], side[1], dec.stream][(i + i // 4) % 4]):
-                got.append(dec.decode(tok, f))
+            with torch.cuda.stream([torch.cuda.default_stream(), side[0], side[1], None, dec._stream][how]):
+                got[i] = dec.decode(tok, f0)
     dec.sync()
     torch.cuda.synchronize()
     for i, (w, g) in enumerate(zip(want, got)):
         assert bits_equal(g.cpu().numpy(), w), f"call {i}"
-    # a reset on the state's stream comes after the caller's calls, a stream reset between them
-    for d in (ref, dec):
-        d.reset()
-    tok, f = cuda(ids[:, :chunk]), cuda(None if f0 is None else f0[:, :chunk * fpt])
-    a = [_home(ref, tok, f, chunk)]
-    b = [dec.decode(tok, f)]
-    ref.reset_stream(1)
-    dec.reset_stream(1)
-    a.append(_home(ref, tok, f, chunk))
-    b.append(dec.decode(tok, f))
+    assert dec.stats()["staged_tokens"] == dec.stats()["calls"] == len(sizes)
+    # a reset on the state's stream comes after the caller's calls
+    got = dec.decode(*inputs[0])
+    dec.reset()
+    again = dec.decode(*inputs[0])
     torch.cuda.synchronize()
-    for w, g in zip(a, b):
-        assert bits_equal(g.cpu().numpy(), w)
-    assert dec.stats()["staged_tokens"] == dec.stats()["calls"]
-    ref.close()
+    assert bits_equal(again.cpu().numpy(), want[0]) and not bits_equal(got.cpu().numpy(), want[0])
+    dec.close()
+
+
+@pytest.mark.parametrize("name,arch,dtype,B,chunk", [CASES[0], CASES[3]], ids=["tiny", "real bf16"])
+def test_work_on_a_held_stream_is_in_order_with_decodes(name, arch, dtype, B, chunk):
+    """A program that keeps Decoder.stream writes each call's tokens and reads its
+    PCM there, while the decodes run on its current stream; nothing is waited for."""
+    blob = synth.make_weights(arch, 0)
+    inputs = _inputs(arch, B, [chunk] * 8)
+    want = _reference(arch, dtype, blob, B, chunk, inputs)
+    dec = dc.Decoder(arch, dtype, blob, B, chunk, chunk, rng_seed=7)
+    held = dec.stream
+    tok = torch.zeros_like(inputs[0][0])
+    got = [torch.empty(w.shape, dtype=torch.float32, device="cuda") for w in want]
+    torch.cuda.synchronize()
+    pcm = []                                    # (kept: their memory is not handed out again)
+    for (t, _), g in zip(inputs, got):
+        with torch.cuda.stream(held):
+            tok.copy_(t)
+        pcm.append(dec.decode(tok))
+        with torch.cuda.stream(held):
+            g.copy_(pcm[-1])
+            tok.zero_()
+    torch.cuda.synchronize()
+    for i, (w, g) in enumerate(zip(want, got)):
+        assert bits_equal(g.cpu().numpy(), w), f"call {i}"
+    dec.close()
+
+
+def test_a_captured_decode_after_an_uncaptured_one():
+    """decode under torch's graph capture (a decoder without graphs of its own; in
+    relaxed mode, as the call allocates its PCM on the state's stream), after a
+    decode on the caller's stream; replays between eager decodes."""
+    arch, B, n = synth.TINY_ARCH, 2, 8
+    blob = synth.make_weights(arch, 0)
+    inputs = _inputs(arch, B, [n] * 8)
+    want = _reference(arch, "f32", blob, B, n, inputs)
+    dec = dc.Decoder(arch, "f32", blob, B, n, n, flags=dc.DC_NO_GRAPH, rng_seed=7)
+    tok = torch.zeros_like(inputs[0][0])
+    first = dec.decode(inputs[0][0])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="relaxed"):
+        pcm = dec.decode(tok)
+    got = [first]
+    for i in range(1, 8):
+        if i % 3 == 0:
+            got.append(dec.decode(inputs[i][0]))
+        else:
+            tok.copy_(inputs[i][0])
+            g.replay()
+            got.append(pcm.clone())
+        if i % 2:
+            torch.cuda.synchronize()
+    torch.cuda.synchronize()
+    for i, (w, o) in enumerate(zip(want, got)):
+        assert bits_equal(o.cpu().numpy(), w), f"call {i}"
+    del g
     dec.close()
 
 
