@@ -267,7 +267,6 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.N = 3 * D;
             g.K = D;
             g.KS = k_steps(D, s->bf);
-        g.KS = k_steps(D, s->bf);
             g.carry = cr;
             gemm_cost("gemm:qkv", 3 * D, D, 4, es, false);
             DCF_TRY(launch_gemm(g, E_QKV, bf, st));
@@ -283,7 +282,6 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.N = D;
             g.K = D;
             g.KS = k_steps(D, s->bf);
-        g.KS = k_steps(D, s->bf);
             g.gate = md + 2 * D;
             gemm_cost("gemm:o", D, D, es, 4, true);
             DCF_TRY(launch_gemm(g, E_RES, bf, st));
@@ -293,7 +291,6 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.N = c.mlp;
             g.K = D;
             g.KS = k_steps(D, s->bf);
-        g.KS = k_steps(D, s->bf);
             g.out = s->u;
             gemm_cost("gemm:fc1", c.mlp, D, 4, es, false);
             DCF_TRY(launch_gemm(g, E_GELU, bf, st));
@@ -303,7 +300,6 @@ hipError_t enqueue_call(dc_flow_state* s, int b0, int Bc, int n, int prompt, con
             g.N = D;
             g.K = c.mlp;
             g.KS = k_steps(c.mlp, s->bf);
-        g.KS = k_steps(c.mlp, s->bf);
             g.gate = md + 5 * D;
             gemm_cost("gemm:fc2", D, c.mlp, es, 4, true);
             DCF_TRY(launch_gemm(g, E_RES, bf, st));
