@@ -19,9 +19,11 @@
  * across states that share the architecture, dtype and batch class: with the
  * automatic tile choice (tile_variant 0) the reduction order of every output
  * sample depends on the layer, the dtype and whether batch < 8 (the streaming
- * class: K split in four partitions) or batch >= 8 (the batched class: one
- * partition, bf16 resblock pairs fused), never on chunk_tokens, max_tokens,
- * the call's n or the stream's index in the batch.  A fresh state whose
+ * class: K split in four partitions, in two for fp32 resblock convs of 64 to 96
+ * channels whose stage's contexts are at most 64 rows) or batch >= 8 (the
+ * batched class: one partition, bf16 resblock pairs fused), never on
+ * chunk_tokens, max_tokens, the call's n or the stream's index in the batch.  A
+ * fresh state whose
  * chunk_tokens covers a whole utterance therefore decodes it to the bits of a
  * chunked decode on a state of the same class.  Across classes the PCM
  * agrees within the rounding tolerance of the dtype, not bit for bit.

@@ -190,13 +190,14 @@ template <> struct OpT<kOpF32> {
 
 // fp32 operands on the bf16 MFMA: every value as the exact sum of three
 // bfloat16 (hi, mid, lo: 8 significant bits each, every residual rounded to
-// nearest), and a product as the six bf16 products of a weight of at least
-// 2^-18 of it, the leading one in an fp32 accumulator of its own, which so is
-// rounded once per 32 channels, the five small ones in another.  What is left
-// out is below 2^-25 of a product, less than its rounding in fp32, and the
-// whole decode is nearer to 64 bits than with fp32 MFMAs (real decoder: 5.2e-7
-// against 7.8e-7).  Six bf16 MFMAs take 6/16 of the time of the fp32 MFMAs for
-// the same products; a value's fragments are 6 bytes instead of 4.
+// nearest; mid is at most 2^-8 of the value, lo 2^-17), and a product as the six
+// bf16 products that can be more than 2^-25 of it, the leading one in an fp32
+// accumulator of its own, which so is rounded once per 32 channels, the five
+// small ones in another.  What is left out (mid lo, lo mid, lo lo) is at most
+// about 2^-24 of a product, the size of one fp32 rounding, and the whole decode
+// is nearer to 64 bits than with fp32 MFMAs (real decoder, these convs only:
+// 7.3e-7 against 7.8e-7).  Six bf16 MFMAs take 6/16 of the time of the fp32 MFMAs
+// for the same products; a value's fragments are 6 bytes instead of 4.
 template <> struct OpT<kOpX3> {
     using T = uint16_t;
     static constexpr int KQ = 32;

@@ -418,7 +418,7 @@ static int pick_variant(const dc_state* s, const ConvOp& op)
     };
     const int kq = op.kq();
     const int kch_all = (op.Ci + kq - 1) / kq;      // chunks covering every input channel
-    // (three planes of fewer than 128 channels: two partitions, for their two
+    // (three planes of at most 96 channels: two partitions, for their two or three
     // chunks of 32; 64 channels at B=1, n=25: 13 us a launch, four 18.5.  With
     // 128 or more two measured slower at B=1, 16.2 us against 13.0, and equal at
     // B=5, n=13: 28 and 29.)
@@ -428,17 +428,20 @@ static int pick_variant(const dc_state* s, const ConvOp& op)
     for (int kch = 32; kch >= 1; kch /= 2) {
         if (kch > kch_all && kch > 1) continue;
         if (wgk == 1 && kch > 4) continue;
-        // fp32 resblock convs of the streaming class (those with contexts too
-        // wide for three planes): channel blocks of at most 128 channels.  The
-        // 256-channel stage's widest tile then stages
-        // 34 KB instead of 68 KB, four blocks fit a CU instead of two, and its
-        // grouped launches run in about one round of blocks instead of two.
+        // fp32 resblock convs of the streaming class on the fp32 MFMA (stages
+        // with a context too wide for three planes): channel blocks of at most
+        // 128 channels.  The 256-channel stage's widest tile then stages half as
+        // much, twice the blocks fit a CU, and its grouped launches run in about
+        // one round of blocks instead of two.  The real decoder with dilations 1,
+        // 3, 7 (contexts of 70 rows): batch 1 n = 25 472 us a call, without the
+        // rule 492; n = 13 378 and 389; batch 5 n = 13 997 and 1010.
         if (wgk == 4 && op.kind() == kOpF32 && op.stage >= 0 && kch > 8) continue;
         // fp32 K-split convs of 256 channels or more with a 50-row left
-        // context (the 256-channel stage at dilation 5): 16x32 tiles, so the
-        // 66 staged rows serve 32 columns per block instead of 16 (the
-        // grouped launch measured 24.9 -> 21.7 us; the 128-channel stage's
-        // 32x32 tiles stay, where 16x32 measured slower)
+        // context or more: 16x32 tiles, so the staged rows serve 32 columns per
+        // block instead of 16 (that decoder's 256-channel launch at dilation 7,
+        // batch 1 n = 25: 22.1 us, 16x16 28.5; n = 13 and batch 5: the same call
+        // time within 0.4%.  The 128-channel stage's 32x32 tiles stay, where
+        // 16x32 measured slower)
         if (wgk == 4 && op.kind() == kOpF32 && op.Ci >= 256 && (op.k - 1) * op.d >= 50) {
             for (int v = 0; v < nv; v++) {
                 const TileShape t = tile_variant(v);

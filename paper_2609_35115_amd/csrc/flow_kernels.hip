@@ -5,10 +5,12 @@
 // with its elementwise tail fused into the epilogue (bias, GELU, the gated
 // residual add, the scatter of keys and values into the carry), a LayerNorm
 // with the step's modulation, and an attention kernel that walks the carried
-// keys and values in place.  The K order of every product is fixed by the
-// layer alone, and rows never interact outside the attention, so a stream's
-// result does not depend on the batch or on which other streams share the
-// call.
+// keys and values in place.  Rows never interact outside the attention, and the
+// order of every sum is fixed by the layer and by two switches on the call's
+// size, at 512 rows (the few-row GEMM, which splits K, and the many-row one) and
+// at 64 blocks of 64 queries (the two attention shapes).  Between calls on the
+// same side of both, a stream's result does not depend on the batch or on which
+// other streams share the call.
 #include <type_traits>
 
 #include "dc_philox.h"

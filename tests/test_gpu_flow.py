@@ -452,8 +452,9 @@ def test_rows_with_a_large_mean_are_normalised_alike(dim):
 
 def test_real_shape_batch20_every_tile_size():
     """20 paper-shaped streams in bf16: 2,240 rows per call, so the MLP-up GEMM
-    takes 128 x 128 tiles, the input, QKV, attention-output and MLP-down GEMMs
-    128 x 64, and the 80-column output projection 32 x 32."""
+    takes 64 x 256 tiles by four waves, the input, QKV, attention-output and
+    MLP-down GEMMs 64 x 256 by eight, and the 80-column output projection
+    16 x 128."""
     a = synth.REAL_FLOW_ARCH
     blob = synth.make_flow_weights(a, 0)
     B, P = 20, 64
