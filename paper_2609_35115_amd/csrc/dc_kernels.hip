@@ -260,9 +260,10 @@ __device__ __forceinline__ void store8_lds(float* dst, const float v[8])
     *(f32x4*)(dst + 4) = b;
 }
 
-// v = hi + mid + lo exactly, planes `stride` elements apart.  A magnitude that
-// rounds past bfloat16 is cut instead, and an infinity or NaN is its own hi
-// with nothing after it.
+// v = hi + mid + lo exactly, planes `stride` elements apart (to 2^-134 where a
+// magnitude below about 2^-110 has its lower planes under bfloat16's range).  A
+// magnitude that rounds past bfloat16 is cut instead, and an infinity or NaN is
+// its own hi with nothing after it.
 __device__ __forceinline__ void store8_lds_x3(uint16_t* dst, int stride, const float v[8])
 {
     u32x4 h, m, l;
