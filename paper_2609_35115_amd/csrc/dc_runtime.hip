@@ -1029,7 +1029,11 @@ static hipError_t enqueue_step(dc_state* s, int n, hipStream_t st, double* ptab 
 static bool capturing(hipStream_t st)
 {
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &c) == hipSuccess && c != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) {   // (the launches that follow will say why)
+        (void)hipGetLastError();
+        return false;
+    }
+    return c != hipStreamCaptureStatusNone;
 }
 
 // Makes the state's own stream ready for work: after the calls made on others.

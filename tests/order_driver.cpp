@@ -79,7 +79,7 @@ static Queue g_default;
 static Clock g_host, g_last;                 // what the host has waited for; the last device operation
 static std::vector<ihipStream_t*> g_free;    // destroyed handles, the next ones to be handed out again
 static std::vector<Queue*> g_captured;
-static int g_unordered = 0, g_ops = 0, g_cap_ops = 0, g_fail_waits = 0, g_fail_syncs = 0;
+static int g_unordered = 0, g_ops = 0, g_cap_ops = 0, g_fail_waits = 0, g_fail_syncs = 0, g_fail_queries = 0;
 static thread_local hipError_t t_err = hipSuccess;
 static std::map<char*, size_t> g_mem;
 
@@ -185,6 +185,7 @@ hipError_t hipStreamDestroy(hipStream_t s) { return g_free.push_back(s), hipSucc
 hipError_t hipStreamSynchronize(hipStream_t s) { return g_host.merge(queue(s).c), hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* out)
 {
+    if (g_fail_queries > 0) return g_fail_queries--, ret(hipErrorStreamCaptureImplicit);
     *out = queue(s).cap ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
@@ -420,6 +421,9 @@ static void callers_error()
         expect((i % 2 ? f.home() : f.on(f.a)) == DC_OK, "a replay after a failed call of the caller's");
         expect(hipGetLastError() == hipErrorOutOfMemory, "whose error is still there");
     }
+    // nor does a query that the runtime refuses leave one (the default stream's, while another is captured)
+    g_fail_queries = 1;
+    expect(f.on(nullptr, 3) == DC_OK && hipGetLastError() == hipSuccess, "direct launches after a refused query");
     expect(dc_sync(f.s) == DC_OK, "a sound state");
 }
 
